@@ -408,13 +408,16 @@ ACCX_API acc_status accx_reduce_dev_noalloc(acc_dtype t, const void *dX, int64_t
 
 /* ---- batched launch --------------------------------------------------------
  * Many independent float32 loop-nest matmuls and reductions on device
- * pointers, run by one hipGraph of two kernels: a packing kernel for every
- * matmul operand, then a persistent kernel whose workgroups take matmul
- * output tiles and reduction chunks from one shared queue.  A matmul runs
- * 128 x 128 tiles when its LEN reaches a threshold, else 64 x 64 (or the
- * tile its flags force); ACC_BATCH_AUTOTUNE picks the threshold by timing
- * the batch itself, otherwise it is 512.  Matmuls in a batch use the
- * six-product bf16x3 split (or ACC_PREC_AUTO's steps, ACC_BATCH_PREC_AUTO);
+ * pointers, run by one hipGraph of two kernels: a prologue that makes the
+ * work queues ready, then a persistent kernel whose workgroups take matmul
+ * output tiles and reduction chunks from them.  Every matmul reads its
+ * operands as they are when the batch is launched, also where an item of the
+ * batch overwrites them (the prologue copies those).  A matmul runs 64 x 64
+ * tiles when its LEN is below a threshold, else 128 x 128 (with
+ * ACC_BATCH_PREC_AUTO also 256 x 128) tiles, or the tile its flags force;
+ * ACC_BATCH_AUTOTUNE picks the threshold by timing the batch itself,
+ * otherwise it is 512.  Matmuls in a batch use the six-product bf16x3 split
+ * (or ACC_PREC_AUTO's steps, ACC_BATCH_PREC_AUTO);
  * a matmul's result is bitwise that of accx_matmul_dev with ACC_PREC_FULL6
  * (ACC_PREC_AUTO) and the same tile, run unsplit (a workspace without the
  * split area).  Reductions are deterministic (fixed chunking, chunk-order
@@ -445,11 +448,11 @@ typedef struct accx_batch_s *accx_batch; /* opaque */
 typedef struct {
     int64_t units;        /* queue entries: matmul tiles + reduction chunks */
     int64_t tiles, chunks;
-    int64_t tile_threshold; /* LEN from which un-forced matmuls take 128 x 128 tiles */
+    int64_t tile_threshold; /* LEN from which un-forced matmuls take 128 x 128 or 256 x 128 tiles */
     int32_t workgroups;   /* persistent workgroups */
     int32_t matmuls, reductions;
     int32_t pad;
-    uint64_t device_bytes;/* descriptors, packed operands, partials */
+    uint64_t device_bytes;/* descriptors, operand copies, partials */
     double flops;         /* sum of 2 n^3 over the matmuls */
     double mfma_flops;    /* bf16 matrix-core flops of the matmuls' main pass (6 or 3 products) */
     double reduce_bytes;  /* sum of 4 n over the reductions */

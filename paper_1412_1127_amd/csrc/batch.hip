@@ -2,36 +2,47 @@
 // section 1.3) and reduction(+) clauses (section 2.3; SRAD paragraph of
 // section 4.2) run as one graph of two kernels:
 //
-//  1. batch_pack: the bf16x3 split of every matmul operand, each operand on
-//     a number of workgroups in proportion to its size (descriptor table of
-//     pack jobs, and the job of each workgroup);
+//  1. batch_prologue: zeroes the queues' counters and the reductions' tickets,
+//     and copies the matmul operands that some item of the batch overwrites;
 //  2. batch_persistent: a persistent kernel (a fixed number of workgroups per
-//     CU) that pulls work units from one queue through an atomic counter:
-//     either one output tile of one matmul (the same LDS-tiled matrix-core
-//     tile as the standalone kernel, in the tile configuration chosen for
-//     that matmul's size class) or one chunk of one reduction.  The queue
+//     CU) that pulls work units from queues through atomic counters: either
+//     one output tile of one matmul, straight from the float32 operands
+//     (direct_tile.h) on the tile configuration chosen for that matmul's
+//     size, or one chunk of one reduction.  There is one queue per XCD, and a
+//     matmul's tiles all sit in one of them, so that they share an L2; a
+//     workgroup whose queue is empty helps with the others.  A queue
 //     interleaves matmul tiles (largest matmuls first) with reduction chunks
 //     so that HBM-bound and matrix-core-bound work share the CUs.
+//
+// What bounds it: 512 matmuls (LEN uniform over 64, 128, ..., 1024) and 256
+// sums (2^16 to 2^24 elements) take 1.60 ms, 1.33 ms with the matmuls alone
+// and 0.50 ms with the sums alone (6.3 TB/s).  They took 2.54 ms while a
+// prepass packed every operand (0.71 ms) for tiles fed by direct-to-LDS
+// loads (1.83 ms); queues per XCD instead of one: 1.85 -> 1.80 ms; 256 x 128
+// tiles beside 128 x 128: 1.80 -> 1.65 ms; a second set of loads in flight in
+// the sums: 1.65 -> 1.60 ms.  In the tile loop (128 x 128, LEN = 4096) the
+// matrix cores are busy 44 % of the cycles, the vector units 34 % (the split
+// is two thirds of that) and the LDS 38 %: with two wavefronts per SIMD their
+// times add up more than they overlap.  Without the split the tile would run
+// 13 % faster, without its loads 30 %, without the probe 12 %; three
+// workgroups per CU of 16-element stages gained 5 % on 128 x 128, less than
+// the larger tile, which they leave no registers for.
 //
 // A reduction's chunk partials are combined by the workgroup that finishes
 // its last chunk (atomic ticket), in chunk order, so results do not depend
 // on which workgroup ran what.  A matmul tile is computed by one workgroup in
 // fixed K order, bitwise as by the standalone kernel in the same tile
-// configuration when that one runs unsplit (no split K).  The last workgroup
-// to leave resets the queue counters, so the graph can be replayed with no
-// memset node.
+// configuration when that one runs unsplit (no split K).
 //
 // Precision: six products (FULL6), or AUTO: the three-product pass of the
-// tile, then the same workgroup probes that tile in float64 (probe_tile:
-// the standalone probe's samples, summed in the order of this kernel's
-// 256-thread workgroups) and, if the tile is
-// marked, adds the three correction products over its 64 x 64 sub-tiles --
-// the standalone AUTO path's steps for that tile, done in place, so no other
-// workgroup and no other launch is involved.
+// tile, then the same workgroup probes that tile in float64 (probe_direct:
+// the standalone probe's samples) and, if the tile is marked, adds the three
+// correction products over it -- the standalone AUTO path's steps for that
+// tile, done in place, so no other workgroup and no other launch is involved.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
-#include "mfma_tile.h"
+#include "direct_tile.h"
 
 namespace accx {
 namespace {
@@ -39,31 +50,33 @@ namespace {
 using namespace dev;
 
 constexpr int BT = 256;              // threads per workgroup (both kernels)
-constexpr int WG_PER_CU = 2;         // persistent workgroups per CU (LDS: 2 x 72 KB)
+constexpr int WG_PER_CU = 2;         // persistent workgroups per CU (LDS: 2 x 72 KB; 256 registers each)
 constexpr uint32_t UNIT_RED = 0x80000000u;
 
-// Tile variants the persistent kernels carry: T128 (first-product
-// look-ahead) and T64; six products (FULL6), or three (CHEAP3) plus the
-// correction products on T64 (AUTO), one kernel per precision.
-#define ACCX_T128(NP, PLIST) false, 3, 128, 128, 32, 2, 2, 3, NP, PLIST, 1, 2
-#define ACCX_T64(NP, PLIST) false, 3, 64, 64, 64, 2, 2, 2, NP, PLIST, 1
+// K elements per LDS stage: a stage holds 24 matrix instructions per
+// wavefront on 256 x 128 and 128 x 128 with either product list, 12 on 64 x
+// 64, and two workgroups' stages fit a CU.
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-constexpr int LDS_MAX = cmax(cmax(gemm_lds_bytes<128, 128, 32, 3, 6, PL_FULL6>(), gemm_lds_bytes<64, 64, 64, 2, 6, PL_FULL6>()),
-                             (int)sizeof(ProbeLds));
-static_assert(LDS_MAX * WG_PER_CU <= 160 * 1024, "persistent kernel LDS");
+constexpr int LDS_MAX = cmax(cmax(direct_lds_bytes<256, 128, 16, 3, PL_CHEAP3>(), direct_lds_bytes<128, 128, 16, 3, PL_CORR3>()),
+                        cmax(cmax(direct_lds_bytes<128, 128, 32, 3, PL_CHEAP3>(), direct_lds_bytes<64, 64, 64, 3, PL_CHEAP3>()),
+                             cmax(direct_lds_bytes<128, 128, 16, 6, PL_FULL6>(), direct_lds_bytes<64, 64, 32, 6, PL_FULL6>())));
+static_assert(LDS_MAX * WG_PER_CU <= 160 * 1024 && sizeof(DirectProbeLds) <= LDS_MAX, "persistent kernel LDS");
 
-// One workgroup of the pack launch: a share of one operand's chunks (the
-// operand's workgroups split its chunks grid-stride among themselves).
-__global__ __launch_bounds__(BT) void batch_pack(const BatchPackJob *__restrict__ jobs,
-                                                 const uint32_t *__restrict__ job_of)
+constexpr int COPY_WGS = 256;  // prologue workgroups per operand copy
+
+// Makes the queue ready for one run of the persistent kernel: workgroup 0
+// zeroes the counters, the others make the operand copies.
+__global__ __launch_bounds__(BT) void batch_prologue(BatchQueue q)
 {
-    const BatchPackJob j = jobs[job_of[blockIdx.x]];
-    const int64_t id0 = (int64_t)(blockIdx.x - j.wg0) * BT + threadIdx.x, step = (int64_t)j.nwg * BT;
-    if (j.trans)
-        pack_bf16x3_range<true>(j.x, j.rows, j.k, j.ld, j.out, j.nrb, j.nkb, id0, step);
-    else
-        pack_bf16x3_range<false>(j.x, j.rows, j.k, j.ld, j.out, j.nrb, j.nkb, id0, step);
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < BATCH_QUEUES) q.counters[threadIdx.x * BATCH_COUNTER_STRIDE] = 0u;
+        for (uint32_t k = threadIdx.x; k < q.nreds; k += BT) *q.reds[k].ticket = 0u;
+        return;
+    }
+    const BatchCopy c = q.copies[(blockIdx.x - 1) / COPY_WGS];
+    const int64_t step = (int64_t)COPY_WGS * BT;
+    for (int64_t k = (int64_t)((blockIdx.x - 1) % COPY_WGS) * BT + threadIdx.x; k < c.n; k += step) c.dst[k] = c.src[k];
 }
 
 __device__ inline float wave_sum_f(float v)
@@ -95,17 +108,30 @@ __device__ __attribute__((always_inline)) inline void reduce_chunk(const BatchRe
     if ((((uintptr_t)(x + b0)) & 15u) == 0) {
         const int64_t nv = (b1 - b0) >> 2;
         const f4v *__restrict__ xv = reinterpret_cast<const f4v *>(x + b0);
-        // eight 16-byte loads in flight per thread
-        f4v acc[8];
+        // two sets of eight 16-byte loads: one in flight while the other is added
+        f4v acc[8], t[2][8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc[u] = (f4v)0;
         int64_t v = threadIdx.x;
-        for (; v + 7 * BT < nv; v += 8 * BT) {
-            f4v t[8];
+        auto load = [&](int64_t at, f4v(&w)[8]) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = __builtin_nontemporal_load(xv + v + u * BT);
+            for (int u = 0; u < 8; ++u) w[u] = __builtin_nontemporal_load(xv + at + u * BT);
+        };
+        auto add = [&](const f4v(&w)[8]) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc[u] += t[u];
+            for (int u = 0; u < 8; ++u) acc[u] += w[u];
+        };
+        if (v + 15 * BT < nv) {
+            load(v, t[0]);
+            load(v + 8 * BT, t[1]);
+            for (v += 16 * BT; v + 15 * BT < nv; v += 16 * BT) {
+                add(t[0]);
+                load(v, t[0]);
+                add(t[1]);
+                load(v + 8 * BT, t[1]);
+            }
+            add(t[0]);
+            add(t[1]);
         }
         for (; v < nv; v += BT) acc[0] += xv[v];
 #pragma unroll
@@ -142,54 +168,63 @@ __device__ __attribute__((always_inline)) inline void reduce_chunk(const BatchRe
     }
 }
 
+template <int BM, int BN, int KS, int NPROD, uint64_t PL>
+__device__ __attribute__((always_inline)) inline void matmul_pass(const DirectArgs &g, int tm, int tn, char *lds,
+                                                                   bool accumulate)
+{
+    f32x16 acc[BM / 64][BN / 64];
+    direct_acc<BM, BN, KS, 2, 2, NPROD, PL>(g, tm, tn, 0, g.K, lds, acc);
+    direct_store<BM, BN, 2, 2>(g, tm, tn, acc, accumulate);
+}
+
+// The three-product pass of a tile; leaves the probe's samples of C in L.
+template <int BM, int BN, int KS>
+__device__ __attribute__((always_inline)) inline void cheap_pass(const DirectArgs &g, int tm, int tn, char *lds,
+                                                                  uint32_t tile)
+{
+    f32x16 acc[BM / 64][BN / 64];
+    direct_acc<BM, BN, KS, 2, 2, 3, PL_CHEAP3>(g, tm, tn, 0, g.K, lds, acc);
+    const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
+    probe_samples<BM, BN, 2, 2>(acc, probe_block(tile, (int)min<int64_t>(BM, g.M - row0), 0),
+                                probe_block(tile, (int)min<int64_t>(BN, g.N - col0), 1),
+                                reinterpret_cast<DirectProbeLds *>(lds)->c);
+    direct_store<BM, BN, 2, 2>(g, tm, tn, acc, false);
+}
+
 template <bool AUTO>
 __device__ __attribute__((always_inline)) inline void matmul_unit(const BatchMat &m, uint32_t tile, char *lds,
                                                                   double tau2)
 {
-    GemmArgs g{};
-    g.A = m.pa;
-    g.B = m.pb;
-    g.C = m.c;
-    g.M = g.N = g.ldc = m.len;
-    g.nkb = m.nkb;
-    g.nrb_a = g.nrb_b = (m.len + 31) / 32;
-    g.tiles_m = m.tiles_m;
-    g.tiles_n = m.tiles_n;
+    const DirectArgs g{m.a, m.b, m.c, m.len, m.len, m.len, m.len, m.len, m.len};
     const int tm = (int)(tile / (uint32_t)m.tiles_n), tn = (int)(tile % (uint32_t)m.tiles_n);
-    const bool t128 = m.tile == GEMM_TILE_128;
     if constexpr (!AUTO) {
-        if (t128)
-            gemm_tile<ACCX_T128(6, PL_FULL6)>(g, tm, tn, lds);
+        if (m.tile == GEMM_TILE_128)
+            matmul_pass<128, 128, 16, 6, PL_FULL6>(g, tm, tn, lds, false);
         else
-            gemm_tile<ACCX_T64(6, PL_FULL6)>(g, tm, tn, lds);
+            matmul_pass<64, 64, 32, 6, PL_FULL6>(g, tm, tn, lds, false);
     } else {
-        if (t128)
-            gemm_tile<ACCX_T128(3, PL_CHEAP3)>(g, tm, tn, lds);
+        if (m.tile == GEMM_TILE_256x128)
+            cheap_pass<256, 128, 16>(g, tm, tn, lds, tile);
+        else if (m.tile == GEMM_TILE_128)
+            cheap_pass<128, 128, 32>(g, tm, tn, lds, tile);
         else
-            gemm_tile<ACCX_T64(3, PL_CHEAP3)>(g, tm, tn, lds);
-        // This tile of C is read back only by this workgroup (probe, then the
-        // correction's read-modify-write), so the barrier's workgroup-scope
-        // release and acquire make it visible; a device-scope fence here
-        // would write back the L2 after every tile.  The LDS stages are free
-        // after the barrier too.
+            cheap_pass<64, 64, 64>(g, tm, tn, lds, tile);
+        const int bm = m.tile == GEMM_TILE_256x128 ? 256 : m.tile == GEMM_TILE_128 ? 128 : 64;
+        const int bn = m.tile == GEMM_TILE_64 ? 64 : 128;
+        if (!probe_direct<BT>(g, bm, bn, tile, tm, tn, tau2, nullptr, *reinterpret_cast<DirectProbeLds *>(lds))) return;
+        // Marked: C += the three correction products.  This tile of C is read
+        // back only by this workgroup, so the barrier's workgroup-scope release
+        // and acquire make it visible; a device-scope fence here would write
+        // back the L2.  The LDS is free after the barrier too.
         __syncthreads();
-        const int bt = t128 ? 128 : 64;
-        if (!probe_tile<BT>(m.pa, m.pb, m.c, m.len, m.len, m.len, m.len, bt, bt, tile, tm, tn, m.nkb, tau2, nullptr,
-                            *reinterpret_cast<ProbeLds *>(lds)))
-            return;
-        // marked: C += the three correction products, on the 64 x 64 tiles
-        // inside this one (those that lie in C), as the standalone correction
-        GemmArgs h = g;
-        h.accumulate = 1;
-        h.tiles_m = h.tiles_n = (int)((m.len + 63) / 64);
-        const int sub = bt / 64;
-        for (int i = 0; i < sub; ++i)
-            for (int j = 0; j < sub; ++j) {
-                const int sm = tm * sub + i, sn = tn * sub + j;
-                if (sm >= h.tiles_m || sn >= h.tiles_n) continue;
-                __syncthreads();  // the LDS stages are reused
-                gemm_tile<ACCX_T64(3, PL_CORR3)>(h, sm, sn, lds);
-            }
+        if (m.tile == GEMM_TILE_64) {
+            matmul_pass<64, 64, 32, 3, PL_CORR3>(g, tm, tn, lds, true);
+        } else {
+            const int sub = bm / 128;
+            for (int q = 0; q < sub; ++q)
+                if ((int64_t)(tm * sub + q) * 128 < g.M)
+                    matmul_pass<128, 128, 16, 3, PL_CORR3>(g, tm * sub + q, tn, lds, true);
+        }
     }
 }
 
@@ -200,29 +235,25 @@ __global__ __launch_bounds__(BT, WG_PER_CU) void batch_persistent(BatchQueue q)
     __shared__ uint32_t cur;
     __shared__ float red4[4];
     __shared__ int is_last;
-    for (;;) {
-        if (threadIdx.x == 0) cur = atomicAdd(q.counter, 1u);
-        __syncthreads();
-        const uint32_t u = cur;
-        __syncthreads();  // every thread has read `cur` before it is rewritten
-        if (u >= q.nunits) break;
+    // This XCD's queue first; once it is empty, the others' in turn.  A queue
+    // that has run out stays empty, so every workgroup leaves after at most
+    // BATCH_QUEUES failed pulls.
+    for (int tries = 0; tries < BATCH_QUEUES;) {
+        const int x = (int)((blockIdx.x + tries) % BATCH_QUEUES);
+        if (threadIdx.x == 0) cur = atomicAdd(q.counters + x * BATCH_COUNTER_STRIDE, 1u);
+        lds_barrier();
+        const uint32_t u = q.first[x] + __builtin_amdgcn_readfirstlane(cur);
+        lds_barrier();  // every thread has read `cur` before it is rewritten
+        if (u >= q.first[x + 1]) {
+            ++tries;
+            continue;
+        }
         const BatchUnit w = q.units[u];
         if (w.item & UNIT_RED)
             reduce_chunk(q.reds[w.item & ~UNIT_RED], w.sub, red4, &is_last);
         else
             matmul_unit<AUTO>(q.mats[w.item], w.sub, lds, q.tau2);
-        __syncthreads();  // LDS and shared scalars are reused by the next unit
-    }
-    // The last workgroup out resets the queue for the next launch.  Only
-    // device-scope atomics take part: each workgroup's last pull from the
-    // counter precedes its exit count in its own program order.  No fence,
-    // which would write back and invalidate this XCD's L2 under the
-    // workgroups still running.
-    if (threadIdx.x == 0) {
-        if (atomicAdd(q.done, 1u) == gridDim.x - 1) {
-            __hip_atomic_store(q.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(q.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        lds_barrier();  // LDS and shared scalars are reused by the next unit
     }
 }
 
@@ -232,18 +263,11 @@ int batch_tile_supported(int tile) { return tile == GEMM_TILE_128 || tile == GEM
 
 int batch_workgroups() { return device_cu_count() * WG_PER_CU; }
 
-int batch_pack_workgroups(int64_t nrb, int64_t nkb)
+hipError_t launch_batch_prologue(const BatchQueue &q, hipStream_t s)
 {
-    const int64_t chunks = nrb * nkb * 128;  // pack_bf16x3_range's work items
-    return (int)std::min<int64_t>(4096, std::max<int64_t>(1, (chunks + BT - 1) / BT));
-}
-
-hipError_t launch_batch_pack(const BatchPackJob *jobs, const uint32_t *job_of, int64_t nwg, hipStream_t s)
-{
-    if (nwg <= 0) return hipSuccess;
-    tmark("batch_pack", s, true);
-    hipLaunchKernelGGL(batch_pack, dim3((unsigned)nwg), dim3(BT), 0, s, jobs, job_of);
-    tmark("batch_pack", s, false);
+    tmark("batch_prologue", s, true);
+    hipLaunchKernelGGL(batch_prologue, dim3(1 + q.ncopies * COPY_WGS), dim3(BT), 0, s, q);
+    tmark("batch_prologue", s, false);
     return hipGetLastError();
 }
 

@@ -189,47 +189,49 @@ hipError_t launch_onbox_read(const void *x, int64_t bytes, hipStream_t s);
 hipError_t launch_fill_hash(void *p, int64_t n, bool as_int, hipStream_t s);
 
 // ---- batched launch (batch.hip) -------------------------------------------
-struct BatchPackJob {   // one bf16x3 operand to pack
-    const float *x;
-    char *out;
-    int64_t rows, k, ld, nrb, nkb;
-    int32_t trans, nwg;    // nwg: the pack launch's workgroups on this operand
-    uint32_t wg0, pad;     // the first of them
-};
-// Workgroups of the pack launch for an operand of nrb 32-row blocks and nkb
-// K units: about one 8-element chunk per thread (at most 4096 workgroups).
-int batch_pack_workgroups(int64_t nrb, int64_t nkb);
-struct BatchMat {       // one matmul: packed operands, output, tiling
-    const char *pa, *pb;
+struct BatchMat {       // one matmul: operands, output, tiling
+    const float *a, *b;
     float *c;
-    int64_t len, nkb;
+    int64_t len;
     int32_t tile, tiles_m, tiles_n, products;
 };
 struct BatchRed {       // one reduction: input, chunking, result slot
     const float *x;
     float *result;
-    uint32_t *ticket;   // zero before the first launch; left at zero
+    uint32_t *ticket;   // zeroed by the prologue launch
     uint32_t *partials; // nchunks words
     int64_t n, chunk;
     int32_t nchunks;
     float init;
 };
+struct BatchCopy {      // a matmul operand that some item of the batch writes: read from a copy
+    const float *src;
+    float *dst;
+    int64_t n;
+};
 struct BatchUnit {      // item index (top bit set: reduction), tile or chunk
     uint32_t item, sub;
 };
+// One work queue per XCD (workgroups are dealt to the 8 XCDs round-robin), so
+// that the tiles of one matmul share one L2.
+constexpr int BATCH_QUEUES = 8;
+constexpr int BATCH_COUNTER_STRIDE = 64;  // words: every counter in lines of its own
 struct BatchQueue {
     const BatchMat *mats;
     const BatchRed *reds;
-    const BatchUnit *units;
-    uint32_t nunits;
-    uint32_t *counter, *done;  // zero before the first launch; left at zero
+    const BatchUnit *units;    // one queue per XCD: units [first[x], first[x + 1])
+    uint32_t first[BATCH_QUEUES + 1];
+    uint32_t *counters;        // BATCH_QUEUES words BATCH_COUNTER_STRIDE apart, zeroed by the prologue launch
+    const BatchCopy *copies;
+    uint32_t nreds, ncopies;
     int32_t auto_prec;         // 1: three products + per-tile float64 probe + correction; 0: six products
     double tau2;               // AUTO: squared relative error bound of the probe
 };
 int batch_tile_supported(int tile);
 int batch_workgroups();
-// job_of[w]: the job of pack workgroup w (nwg workgroups in all).
-hipError_t launch_batch_pack(const BatchPackJob *jobs, const uint32_t *job_of, int64_t nwg, hipStream_t s);
+// Zero the queue's counter and the reductions' tickets and make the operand
+// copies; must precede every persistent launch on its stream.
+hipError_t launch_batch_prologue(const BatchQueue &q, hipStream_t s);
 hipError_t launch_batch_persistent(const BatchQueue &q, hipStream_t s);
 
 int device_cu_count();  // compute units of the current device (cached)

@@ -329,6 +329,16 @@ __device__ inline uint32_t word_of(int v) { return (uint32_t)v; }
 // expcnt and lgkmcnt left at their maxima).
 template <int N> constexpr int vmcnt_imm() { return (N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14); }
 
+// A barrier of the workgroup that orders LDS accesses only: global loads and
+// stores stay in flight across it (__syncthreads waits for them).
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // One workgroup computes the BM x BN tile (tm, tn) of C with WGM x WGN
 // wavefronts, staging operands in `lds` (gemm_lds_bytes bytes, 1 KB aligned).
 // The K loop runs over K-steps of KBK bytes per row per plane, staged in LDS
@@ -865,11 +875,14 @@ constexpr int PROBE_NW = 8;          // wavefronts of a probing workgroup, at mo
 // consecutive rows of a packed operand share each 128-byte line of a 16-byte
 // K chunk (rows are 16 bytes apart in a unit), so the probe reads whole
 // lines; rows spread over the tile would use 16 bytes of each.
-__device__ inline int probe_pick(int64_t key, int k, int extent, int salt)
+__device__ inline int probe_block(int64_t key, int extent, int salt)
 {
     const int blocks = (extent + PS - 1) / PS;
-    const int b = (int)(hash32((uint32_t)(key * 2 + salt) * 2654435761u + 977u) % (uint32_t)blocks);
-    const int v = b * PS + k;
+    return (int)(hash32((uint32_t)(key * 2 + salt) * 2654435761u + 977u) % (uint32_t)blocks);
+}
+__device__ inline int probe_pick(int64_t key, int k, int extent, int salt)
+{
+    const int v = probe_block(key, extent, salt) * PS + k;
     return v < extent ? v : extent - 1;
 }
 
@@ -878,6 +891,78 @@ struct ProbeLds {
     double part[PROBE_NW][PS * PS];
     int marked;
 };
+
+// One step of the probe's butterfly: at mask O a lane keeps the half of its C
+// live sums that its lane bit O selects and adds its partner's copy of that
+// half.  (Steps by template: as one loop over a masked array argument the
+// compiler left the sums in scratch memory.)
+template <int O, int C> __device__ __attribute__((always_inline)) inline void probe_fold(double *acc, int lane)
+{
+    if constexpr (O > 0) {
+        const bool hi = (lane & O) != 0;
+#pragma unroll
+        for (int z = 0; z < C / 2; ++z) {
+            const double keep = hi ? acc[z + C / 2] : acc[z];
+            const double send = hi ? acc[z] : acc[z + C / 2];
+            acc[z] = keep + __shfl_xor(send, O, 64);
+        }
+        probe_fold<O / 2, C / 2>(acc, lane);
+    }
+}
+
+// The last step of a tile's probe, by a workgroup of WAVES wavefronts: acc
+// holds this thread's partial float64 sums of half of the samples, the lower
+// or the upper lanes' half; lane l ends with the sum in place l % 32 of its
+// half's, which is sample (u, v) of the tile.  Adds them up, compares with C (cs: the samples of C, in
+// LDS; NULL: read from C), decides, and writes the record (nullable).
+// Returns the decision in every thread.
+template <int WAVES>
+__device__ __attribute__((always_inline)) inline bool probe_finish(double (&acc)[PS * PS / 2], int u, int v,
+                                                                   const float *cs, const float *C, int64_t ldc, int64_t row0, int64_t col0, int rext,
+                                                                   int cext, int64_t tile, double tau2,
+                                                                   ProbeRecord *__restrict__ rec,
+                                                                   double (*part)[PS * PS], int *marked_out)
+{
+    constexpr int HS = PS * PS / 2;
+    const int q = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // butterfly over the half-wavefront; lane l ends with acc[0] = the
+    // wavefront's sum for sample l
+    probe_fold<16, HS>(acc, q);
+    part[wave][q] = acc[0];
+    lds_barrier();
+    // wavefront 0, one sample per lane: compare, then sum the squares over
+    // the wavefront (a fixed butterfly: every lane ends with the same sums)
+    if (threadIdx.x < 64) {
+        const int64_t row = row0 + probe_pick(tile, u, rext, 0), col = col0 + probe_pick(tile, v, cext, 1);
+        double ref = part[0][q];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) ref += part[w][q];
+        const double c = cs ? (double)cs[PS * u + v] : (double)C[row * ldc + col];
+        double e2 = (c - ref) * (c - ref), r2 = ref * ref;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            e2 += __shfl_xor(e2, o, 64);
+            r2 += __shfl_xor(r2, o, 64);
+        }
+        const int marked = (r2 > 0.0) ? (e2 > tau2 * r2) : (e2 > 0.0);
+        if (rec) {
+            rec->ref[PS * u + v] = ref;
+            if (q < PS) {
+                rec->rows[q] = (int32_t)(row0 + probe_pick(tile, q, rext, 0));
+                rec->cols[q] = (int32_t)(col0 + probe_pick(tile, q, cext, 1));
+            }
+            if (q == 0) {
+                rec->err2 = e2;
+                rec->ref2 = r2;
+                rec->corrected = marked;
+                rec->pad[0] = rec->pad[1] = rec->pad[2] = 0;
+            }
+        }
+        if (q == 0) *marked_out = marked;
+    }
+    lds_barrier();
+    return *marked_out != 0;
+}
 
 // The float64 error probe of one output tile (tile index `tile` = tm *
 // tiles_n + tn, bm x bn) of a cheap-pass result C (m x n, leading dimension
@@ -1013,55 +1098,8 @@ __device__ __attribute__((always_inline)) inline bool probe_tile(const char *__r
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     }
-    // butterfly over the half-wavefront: at mask o a lane keeps the half of
-    // its c live sums that its lane bit o selects and adds its partner's
-    // copy of that half; lane l ends with acc[0] = the wavefront's sum for
-    // sample l
-#pragma unroll
-    for (int o = 16, c = HS; o > 0; o >>= 1, c >>= 1) {
-        const bool hi = (q & o) != 0;
-#pragma unroll
-        for (int z = 0; z < c / 2; ++z) {
-            const double keep = hi ? acc[z + c / 2] : acc[z];
-            const double send = hi ? acc[z] : acc[z + c / 2];
-            acc[z] = keep + __shfl_xor(send, o, 64);
-        }
-    }
-    L.part[wave][q] = acc[0];
-    __syncthreads();
-    // wavefront 0, one sample per lane: compare, then sum the squares over
-    // the wavefront (a fixed butterfly: every lane ends with the same sums)
-    if (threadIdx.x < 64) {
-        const int u = q / PS, v = q % PS;
-        const int64_t row = row0 + probe_pick(tile, u, rext, 0), col = col0 + probe_pick(tile, v, cext, 1);
-        double ref = L.part[0][q];
-#pragma unroll
-        for (int w = 1; w < WAVES; ++w) ref += L.part[w][q];
-        const double c = (double)C[row * ldc + col];
-        double e2 = (c - ref) * (c - ref), r2 = ref * ref;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            e2 += __shfl_xor(e2, o, 64);
-            r2 += __shfl_xor(r2, o, 64);
-        }
-        const int marked = (r2 > 0.0) ? (e2 > tau2 * r2) : (e2 > 0.0);
-        if (rec) {
-            rec->ref[q] = ref;
-            if (q < PS) {
-                rec->rows[q] = (int32_t)(row0 + probe_pick(tile, q, rext, 0));
-                rec->cols[q] = (int32_t)(col0 + probe_pick(tile, q, cext, 1));
-            }
-            if (q == 0) {
-                rec->err2 = e2;
-                rec->ref2 = r2;
-                rec->corrected = marked;
-                rec->pad[0] = rec->pad[1] = rec->pad[2] = 0;
-            }
-        }
-        if (q == 0) L.marked = marked;
-    }
-    __syncthreads();
-    return L.marked != 0;
+    return probe_finish<WAVES>(acc, q / PS, q % PS, nullptr, C, ldc, row0, col0, rext, cext, tile, tau2, rec, L.part,
+                               &L.marked);
 }
 
 }  // namespace dev

@@ -2023,13 +2023,9 @@ void device_free(void *p)
 // Batched launch: plan, graph, launch.
 
 struct accx_batch_s {
-    void *dev = nullptr;  // one allocation: descriptors, queue, counters, partials, packed operands
+    void *dev = nullptr;  // one allocation: descriptors, queue, counters, partials
     size_t dev_bytes = 0;
     accx::BatchQueue queue{};
-    accx::BatchPackJob *jobs = nullptr;  // device
-    int njobs = 0;
-    uint32_t *job_of = nullptr;          // device: the job of each pack workgroup
-    int64_t pack_wgs = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     accx_batch_info_t info{};
@@ -2045,52 +2041,85 @@ std::set<accx_batch_s *> &batches()
     return *b;
 }
 
-// Tile policy of a batch: an item's forced tile, else 128 x 128 when its
-// LEN is at least `threshold`, else 64 x 64.
-int batch_tile(const accx_batch_item &it, int64_t threshold)
+// Relative time of one output element on each tile a batch runs, per step of
+// K (measured on 128 matmuls of LEN = 1024: 886, 798 and 465 TFLOP/s of bf16
+// products on 256 x 128, 128 x 128 and 64 x 64).
+double batch_tile_cost(int tile) { return tile == accx::GEMM_TILE_256x128 ? 0.9 : tile == accx::GEMM_TILE_128 ? 1.0 : 1.7; }
+
+void batch_tile_dims(int tile, int &bm, int &bn)
+{
+    bm = tile == accx::GEMM_TILE_256x128 ? 256 : tile == accx::GEMM_TILE_128 ? 128 : 64;
+    bn = std::min(bm, 128);
+}
+
+// Tile policy of a batch: an item's forced tile, else 64 x 64 when its LEN
+// is below `threshold`, else 128 x 128 or (AUTO batches) 256 x 128, whichever
+// covers the result at the lower cost, padding included.
+int batch_tile(const accx_batch_item &it, int64_t threshold, bool auto_prec)
 {
     const int forced = (int)((it.flags & ACC_TILE_MASK) >> ACC_TILE_SHIFT);
     if (forced) return forced;
-    return it.n >= threshold ? accx::GEMM_TILE_128 : accx::GEMM_TILE_64;
+    if (it.n < threshold) return accx::GEMM_TILE_64;
+    if (!auto_prec) return accx::GEMM_TILE_128;
+    const int64_t t128 = (it.n + 127) / 128, t256 = (it.n + 255) / 256;
+    return 2.0 * t256 * t128 * batch_tile_cost(accx::GEMM_TILE_256x128) <
+                   1.0 * t128 * t128 * batch_tile_cost(accx::GEMM_TILE_128)
+               ? accx::GEMM_TILE_256x128
+               : accx::GEMM_TILE_128;
 }
 
 constexpr int64_t kBatchDefaultThreshold = 512;
 
-// Work queue for the given tiles: matmul tiles, largest matmul first, with
-// the reduction chunks spread evenly through it by cumulative cost, so that
-// both kinds of work are in flight throughout.
-std::vector<accx::BatchUnit> batch_units(std::vector<accx::BatchMat> &mats, const std::vector<accx::BatchRed> &reds)
+// Work queues for the given tiles, one per XCD (first[x] .. first[x + 1] of
+// the returned units).  A matmul goes whole to one queue, so that its tiles
+// share that XCD's L2: largest first, each to the queue with the least work
+// so far; the reductions' chunks are dealt out evenly.  Within a queue: matmul
+// tiles, largest matmul first, with the reduction chunks spread evenly
+// through them by cumulative cost, so that both kinds of work are in flight
+// throughout.
+std::vector<accx::BatchUnit> batch_units(std::vector<accx::BatchMat> &mats, const std::vector<accx::BatchRed> &reds,
+                                         uint32_t *first)
 {
+    constexpr int Q = accx::BATCH_QUEUES;
     std::vector<int> order(mats.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return mats[x].len > mats[y].len; });
-    std::vector<std::pair<double, accx::BatchUnit>> mu, ru;
-    double mtot = 0, rtot = 0;
+    using Costed = std::vector<std::pair<double, accx::BatchUnit>>;  // (work before it in its list, unit)
+    Costed mu[Q], ru[Q];
+    double mtot[Q] = {}, rtot[Q] = {};
     for (int k : order) {
         accx::BatchMat &m = mats[k];
-        const int bm = m.tile == accx::GEMM_TILE_128 ? 128 : 64;
-        m.tiles_m = m.tiles_n = (int32_t)((m.len + bm - 1) / bm);
+        int bm, bn;
+        batch_tile_dims(m.tile, bm, bn);
+        m.tiles_m = (int32_t)((m.len + bm - 1) / bm);
+        m.tiles_n = (int32_t)((m.len + bn - 1) / bn);
+        const int x = (int)(std::min_element(mtot, mtot + Q) - mtot);
         for (int t = 0; t < m.tiles_m * m.tiles_n; ++t) {
-            mu.push_back({mtot, accx::BatchUnit{(uint32_t)k, (uint32_t)t}});
-            mtot += (double)bm * bm * (double)m.len;
+            mu[x].push_back({mtot[x], accx::BatchUnit{(uint32_t)k, (uint32_t)t}});
+            mtot[x] += (double)bm * bn * (double)m.len * batch_tile_cost(m.tile);
         }
     }
+    int deal = 0;
     for (size_t k = 0; k < reds.size(); ++k)
         for (int32_t c = 0; c < reds[k].nchunks; ++c) {
-            ru.push_back({rtot, accx::BatchUnit{(uint32_t)k | 0x80000000u, (uint32_t)c}});
-            rtot += (double)std::min<int64_t>(reds[k].chunk, std::max<int64_t>(0, reds[k].n - c * reds[k].chunk));
+            const int x = deal++ % Q;
+            ru[x].push_back({rtot[x], accx::BatchUnit{(uint32_t)k | 0x80000000u, (uint32_t)c}});
+            rtot[x] += (double)std::min<int64_t>(reds[k].chunk, std::max<int64_t>(0, reds[k].n - c * reds[k].chunk));
         }
     std::vector<accx::BatchUnit> units;
-    units.reserve(mu.size() + ru.size());
-    size_t im = 0, ir = 0;
-    while (im < mu.size() || ir < ru.size()) {
-        const double fm = im < mu.size() ? (mtot > 0 ? mu[im].first / mtot : 0) : 2.0;
-        const double fr = ir < ru.size() ? (rtot > 0 ? ru[ir].first / rtot : 0) : 2.0;
-        if (fm <= fr)
-            units.push_back(mu[im++].second);
-        else
-            units.push_back(ru[ir++].second);
+    for (int x = 0; x < Q; ++x) {
+        first[x] = (uint32_t)units.size();
+        size_t im = 0, ir = 0;
+        while (im < mu[x].size() || ir < ru[x].size()) {
+            const double fm = im < mu[x].size() ? (mtot[x] > 0 ? mu[x][im].first / mtot[x] : 0) : 2.0;
+            const double fr = ir < ru[x].size() ? (rtot[x] > 0 ? ru[x][ir].first / rtot[x] : 0) : 2.0;
+            if (fm <= fr)
+                units.push_back(mu[x][im++].second);
+            else
+                units.push_back(ru[x][ir++].second);
+        }
     }
+    first[Q] = (uint32_t)units.size();
     return units;
 }
 
@@ -2115,7 +2144,7 @@ void batch_release(accx_batch_s *b)
 
 hipError_t batch_enqueue(accx_batch_s *b, hipStream_t s)
 {
-    hipError_t e = accx::launch_batch_pack(b->jobs, b->job_of, b->pack_wgs, s);
+    hipError_t e = accx::launch_batch_prologue(b->queue, s);
     if (e == hipSuccess) e = accx::launch_batch_persistent(b->queue, s);
     return e;
 }
@@ -2141,7 +2170,6 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
     std::vector<accx::BatchRed> reds;
     std::vector<int> mat_item;
     std::vector<int64_t> red_chunks;
-    std::vector<size_t> pk_bytes;
     accx_batch_info_t info{};
     int64_t max_tiles = 0;  // queue bound over every tile policy (all 64 x 64)
     for (int i = 0; i < nitems; ++i) {
@@ -2158,14 +2186,14 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
             if (forced && !accx::batch_tile_supported(forced))
                 return fail(ACC_ERR_INVALID_ARG, where + "batches run ACC_TILE_128 or ACC_TILE_64");
             accx::BatchMat m{};
+            m.a = static_cast<const float *>(it.a);
+            m.b = static_cast<const float *>(it.b);
             m.c = static_cast<float *>(it.c);
             m.len = it.n;
-            m.nkb = (it.n * 2 + 63) / 64;
-            m.tile = batch_tile(it, kBatchDefaultThreshold);
+            m.tile = batch_tile(it, kBatchDefaultThreshold, auto_prec);
             m.products = products;
             mats.push_back(m);
             mat_item.push_back(i);
-            pk_bytes.push_back(accx::packed_bytes(it.n, it.n, 2, 3));
             max_tiles += ((it.n + 63) / 64) * ((it.n + 63) / 64);
             info.flops += 2.0 * (double)it.n * (double)it.n * (double)it.n;
             info.mfma_flops += products * 2.0 * (double)it.n * (double)it.n * (double)it.n;
@@ -2191,7 +2219,8 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         }
     }
     if (max_tiles + info.chunks >= (int64_t)0x7fffffff) return fail(ACC_ERR_INVALID_ARG, "batch too large");
-    std::vector<accx::BatchUnit> units = batch_units(mats, reds);
+    uint32_t first[accx::BATCH_QUEUES + 1];
+    std::vector<accx::BatchUnit> units = batch_units(mats, reds, first);
     const size_t max_units = (size_t)(max_tiles + info.chunks);
 
     // Device layout.
@@ -2203,20 +2232,48 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
     off = al(off + sizeof(accx::BatchRed) * std::max<size_t>(1, reds.size()));
     const size_t o_units = off;
     off = al(off + sizeof(accx::BatchUnit) * std::max<size_t>(1, max_units));
-    const size_t o_jobs = off;
-    off = al(off + sizeof(accx::BatchPackJob) * std::max<size_t>(1, 2 * mats.size()));
-    // pack workgroups: A and B^T of matmul k get batch_pack_workgroups each
-    int64_t pack_wgs = 0;
-    for (size_t k = 0; k < mats.size(); ++k)
-        pack_wgs += 2 * (int64_t)accx::batch_pack_workgroups((mats[k].len + 31) / 32, mats[k].nkb);
-    const size_t o_jobof = off;
-    off = al(off + sizeof(uint32_t) * (size_t)std::max<int64_t>(1, pack_wgs));
+    // Matmul operands that overlap an output of the batch (in-place nests, one
+    // item's result inside another's operand) are read from copies made by
+    // the prologue: every matmul sees its operands as they are at the launch.
+    std::vector<accx::BatchCopy> copies;
+    std::vector<const float **> copy_of;
+    size_t copy_bytes = 0;
+    {
+        std::vector<std::pair<uintptr_t, uintptr_t>> outs;  // merged output ranges, ascending
+        for (const accx::BatchMat &m : mats)
+            outs.push_back({(uintptr_t)m.c, (uintptr_t)m.c + (size_t)m.len * m.len * 4});
+        for (const accx::BatchRed &r : reds) outs.push_back({(uintptr_t)r.result, (uintptr_t)r.result + 4});
+        std::sort(outs.begin(), outs.end());
+        size_t w = 0;
+        for (size_t k = 1; k < outs.size(); ++k) {
+            if (outs[k].first <= outs[w].second)
+                outs[w].second = std::max(outs[w].second, outs[k].second);
+            else
+                outs[++w] = outs[k];
+        }
+        if (!outs.empty()) outs.resize(w + 1);
+        auto written = [&](const float *p, int64_t n) {
+            const uintptr_t b = (uintptr_t)p, e = b + (size_t)n * 4;
+            auto it = std::upper_bound(outs.begin(), outs.end(), std::make_pair(b, ~(uintptr_t)0));
+            return (it != outs.begin() && std::prev(it)->second > b) || (it != outs.end() && it->first < e);
+        };
+        for (accx::BatchMat &m : mats)
+            for (const float **x : {&m.a, &m.b})
+                if (written(*x, m.len * m.len)) {
+                    copies.push_back(accx::BatchCopy{*x, nullptr, m.len * m.len});
+                    copy_of.push_back(x);
+                    copy_bytes += al((size_t)m.len * m.len * 4);
+                }
+        if (copies.size() > ((size_t)1 << 22)) return fail(ACC_ERR_INVALID_ARG, "batch too large");
+    }
+    const size_t o_copies = off;
+    off = al(off + sizeof(accx::BatchCopy) * std::max<size_t>(1, copies.size()));
+    const size_t o_copy = off;
+    off += copy_bytes;
     const size_t o_zero = off;  // counters, tickets, partials: zero-filled
-    size_t zbytes = 256;
+    size_t zbytes = 4 * accx::BATCH_QUEUES * accx::BATCH_COUNTER_STRIDE;
     for (size_t k = 0; k < reds.size(); ++k) zbytes += 4 + 4 * (size_t)reds[k].nchunks;
     off = al(off + zbytes);
-    const size_t o_pack = off;
-    for (size_t k = 0; k < mats.size(); ++k) off = al(off + 2 * pk_bytes[k]);
 
     accx_batch_s *b = new (std::nothrow) accx_batch_s();
     if (!b) return fail(ACC_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -2226,50 +2283,31 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
     }
     b->dev_bytes = off;
     char *base = static_cast<char *>(b->dev);
-    std::vector<accx::BatchPackJob> jobs;
-    std::vector<uint32_t> job_of;
-    job_of.reserve((size_t)pack_wgs);
     {
-        size_t p = o_pack;
-        for (size_t k = 0; k < mats.size(); ++k) {
-            const accx_batch_item &it = items[mat_item[k]];
-            char *pa = base + p, *pb = base + p + pk_bytes[k];
-            p = al(p + 2 * pk_bytes[k]);
-            mats[k].pa = pa;
-            mats[k].pb = pb;
-            const int64_t nrb = (it.n + 31) / 32;
-            const int nwg = accx::batch_pack_workgroups(nrb, mats[k].nkb);
-            for (int t = 0; t < 2; ++t) {
-                jobs.push_back(accx::BatchPackJob{static_cast<const float *>(t ? it.b : it.a), t ? pb : pa, it.n,
-                                                  it.n, it.n, nrb, mats[k].nkb, t, nwg, (uint32_t)job_of.size(), 0});
-                job_of.insert(job_of.end(), (size_t)nwg, (uint32_t)(jobs.size() - 1));
-            }
-        }
         uint32_t *z = reinterpret_cast<uint32_t *>(base + o_zero);
-        size_t w = 64;  // counter at word 0, done at word 1
+        size_t w = accx::BATCH_QUEUES * accx::BATCH_COUNTER_STRIDE;  // the queues' counters first
         for (size_t k = 0; k < reds.size(); ++k) {
             reds[k].ticket = z + w;
             reds[k].partials = z + w + 1;
             w += 1 + (size_t)reds[k].nchunks;
         }
-        b->queue.counter = z;
-        b->queue.done = z + 1;
+        b->queue.counters = z;
+        b->queue.nreds = (uint32_t)reds.size();
+        size_t p = o_copy;
+        for (size_t k = 0; k < copies.size(); ++k) {
+            copies[k].dst = reinterpret_cast<float *>(base + p);
+            *copy_of[k] = copies[k].dst;
+            p += al((size_t)copies[k].n * 4);
+        }
+        b->queue.copies = reinterpret_cast<const accx::BatchCopy *>(base + o_copies);
+        b->queue.ncopies = (uint32_t)copies.size();
     }
     b->queue.auto_prec = auto_prec ? 1 : 0;
     b->queue.tau2 = probe_tau() * probe_tau();
     b->queue.mats = reinterpret_cast<const accx::BatchMat *>(base + o_mats);
     b->queue.reds = reinterpret_cast<const accx::BatchRed *>(base + o_reds);
     b->queue.units = reinterpret_cast<const accx::BatchUnit *>(base + o_units);
-    b->queue.nunits = (uint32_t)units.size();
-    b->jobs = reinterpret_cast<accx::BatchPackJob *>(base + o_jobs);
-    b->njobs = (int)jobs.size();
-    b->job_of = reinterpret_cast<uint32_t *>(base + o_jobof);
-    b->pack_wgs = (int64_t)job_of.size();
-    if (b->pack_wgs != pack_wgs || pack_wgs >= ((int64_t)1 << 31)) {  // the layout's count, and one launch's grid
-        dev_free(b->dev, b->dev_bytes);
-        delete b;
-        return fail(ACC_ERR_INVALID_ARG, "batch too large");
-    }
+    std::copy(first, first + accx::BATCH_QUEUES + 1, b->queue.first);
 
     hipError_t e = hipSuccess;
     hipStream_t cs = nullptr;
@@ -2278,10 +2316,8 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         e = hipMemcpy(base + o_reds, reds.data(), sizeof(accx::BatchRed) * reds.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !units.empty())
         e = hipMemcpy(base + o_units, units.data(), sizeof(accx::BatchUnit) * units.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !jobs.empty())
-        e = hipMemcpy(base + o_jobs, jobs.data(), sizeof(accx::BatchPackJob) * jobs.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !job_of.empty())
-        e = hipMemcpy(base + o_jobof, job_of.data(), sizeof(uint32_t) * job_of.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !copies.empty())
+        e = hipMemcpy(base + o_copies, copies.data(), sizeof(accx::BatchCopy) * copies.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(base + o_zero, 0, zbytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     int64_t threshold = kBatchDefaultThreshold;
@@ -2293,20 +2329,19 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (e == hipSuccess) e = hipEventCreate(&e0);
         if (e == hipSuccess) e = hipEventCreate(&e1);
-        if (e == hipSuccess) e = accx::launch_batch_pack(b->jobs, b->job_of, b->pack_wgs, cs);
         double best = 1e300;
         const int64_t cand[] = {0, 192, 320, 448, 576, 768, 65537};
         for (int64_t th : cand) {
             if (e != hipSuccess) break;
-            for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[mat_item[k]], th);
-            std::vector<accx::BatchUnit> u = batch_units(mats, reds);
-            b->queue.nunits = (uint32_t)u.size();
+            for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[mat_item[k]], th, auto_prec);
+            std::vector<accx::BatchUnit> u = batch_units(mats, reds, b->queue.first);
             e = hipMemcpy(base + o_mats, mats.data(), sizeof(accx::BatchMat) * mats.size(), hipMemcpyHostToDevice);
             if (e == hipSuccess)
                 e = hipMemcpy(base + o_units, u.data(), sizeof(accx::BatchUnit) * u.size(), hipMemcpyHostToDevice);
             double t_best = 1e300;
             for (int r = 0; r < 3 && e == hipSuccess; ++r) {
-                e = hipEventRecord(e0, cs);
+                e = accx::launch_batch_prologue(b->queue, cs);
+                if (e == hipSuccess) e = hipEventRecord(e0, cs);
                 if (e == hipSuccess) e = accx::launch_batch_persistent(b->queue, cs);
                 if (e == hipSuccess) e = hipEventRecord(e1, cs);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -2324,9 +2359,8 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         if (cs) (void)hipStreamDestroy(cs);
         cs = nullptr;
         if (e == hipSuccess) {
-            for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[mat_item[k]], threshold);
-            units = batch_units(mats, reds);
-            b->queue.nunits = (uint32_t)units.size();
+            for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[mat_item[k]], threshold, auto_prec);
+            units = batch_units(mats, reds, b->queue.first);
             e = hipMemcpy(base + o_mats, mats.data(), sizeof(accx::BatchMat) * mats.size(), hipMemcpyHostToDevice);
             if (e == hipSuccess)
                 e = hipMemcpy(base + o_units, units.data(), sizeof(accx::BatchUnit) * units.size(),
