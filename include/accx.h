@@ -140,7 +140,9 @@ typedef struct acc_region_s *acc_region; /* opaque */
 #define ACC_ASYNC 0x1000u
 /* tile configuration of the tiled kernel (bits 16..19).  AUTO takes the
  * autotuner's choice for the size class (see accx_autotune), else a size
- * heuristic; the others force one configuration. */
+ * heuristic (which also decides whether a float32 product of few tiles runs
+ * straight from its operands, with no packing prepass); the others force one
+ * configuration of the packed path. */
 #define ACC_TILE_SHIFT 16
 #define ACC_TILE_MASK 0xF0000u
 #define ACC_TILE_AUTO 0x00000u

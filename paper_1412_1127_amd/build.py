@@ -24,6 +24,7 @@ SOURCES = [
     "matmul_plain.hip",
     "reduce.hip",
     "gemm_mfma.hip",
+    "gemm_direct.hip",
     "batch.hip",
     "onbox.hip",
 ]

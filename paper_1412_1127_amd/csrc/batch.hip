@@ -173,8 +173,8 @@ __device__ __attribute__((always_inline)) inline void matmul_pass(const DirectAr
                                                                    bool accumulate)
 {
     f32x16 acc[BM / 64][BN / 64];
-    direct_acc<BM, BN, KS, 2, 2, NPROD, PL>(g, tm, tn, 0, g.K, lds, acc);
-    direct_store<BM, BN, 2, 2>(g, tm, tn, acc, accumulate);
+    direct_acc<BM, BN, KS, 2, 2, NPROD, PL>(g, tm, tn, 0, g.K, threadIdx.x, 0, lds, acc);
+    direct_store<BM, BN, 2, 2>(g, tm, tn, threadIdx.x, acc, accumulate);
 }
 
 // The three-product pass of a tile; leaves the probe's samples of C in L.
@@ -183,12 +183,12 @@ __device__ __attribute__((always_inline)) inline void cheap_pass(const DirectArg
                                                                   uint32_t tile)
 {
     f32x16 acc[BM / 64][BN / 64];
-    direct_acc<BM, BN, KS, 2, 2, 3, PL_CHEAP3>(g, tm, tn, 0, g.K, lds, acc);
+    direct_acc<BM, BN, KS, 2, 2, 3, PL_CHEAP3>(g, tm, tn, 0, g.K, threadIdx.x, 0, lds, acc);
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
-    probe_samples<BM, BN, 2, 2>(acc, probe_block(tile, (int)min<int64_t>(BM, g.M - row0), 0),
+    probe_samples<BM, BN, 2, 2>(acc, threadIdx.x, probe_block(tile, (int)min<int64_t>(BM, g.M - row0), 0),
                                 probe_block(tile, (int)min<int64_t>(BN, g.N - col0), 1),
                                 reinterpret_cast<DirectProbeLds *>(lds)->c);
-    direct_store<BM, BN, 2, 2>(g, tm, tn, acc, false);
+    direct_store<BM, BN, 2, 2>(g, tm, tn, threadIdx.x, acc, false);
 }
 
 template <bool AUTO>

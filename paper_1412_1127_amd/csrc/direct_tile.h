@@ -70,14 +70,17 @@ template <int BM, int BN, int KS, int NPROD, uint64_t PL> constexpr int direct_l
 }
 
 // acc = sum over k in [kb, ke) of the product list on tile (tm, tn), by
-// WGM x WGN wavefronts.  Two LDS stages of KS elements; the float32 operands
-// of the stage after next are in flight in registers while a stage is
-// computed: one barrier per stage.  Rows past M and columns past N read the
-// last row or column (their outputs are not stored); elements past ke are
-// zero in both operands.
+// WGM x WGN wavefronts: a whole workgroup, or one of its groups of that many,
+// each with an LDS area of its own (t: the thread's index in its group).  Two
+// LDS stages of KS elements; the float32 operands of the stage after next are
+// in flight in registers while a stage is computed: one barrier of the
+// workgroup per stage, `barriers` stages' worth in all, so that groups with
+// fewer stages keep step.  Rows past M and columns past N read the last row
+// or column (their outputs are not stored); elements past ke are zero in both
+// operands.
 template <int BM, int BN, int KS, int WGM, int WGN, int NPROD, uint64_t PL>
 __device__ __attribute__((always_inline)) inline void direct_acc(const DirectArgs &g, int tm, int tn, int64_t kb,
-                                                                 int64_t ke, char *lds,
+                                                                 int64_t ke, int t, int barriers, char *lds,
                                                                  f32x16 (&acc)[BM / 32 / WGM][BN / 32 / WGN])
 {
     constexpr int THREADS = WGM * WGN * 64;
@@ -88,7 +91,7 @@ __device__ __attribute__((always_inline)) inline void direct_acc(const DirectArg
     constexpr int CG = THREADS / BN, NBC = (KS / 8) / CG;          // B: chunks per pass, passes
     static_assert(BM % RPP == 0 && THREADS % BN == 0 && (KS / 8) % CG == 0, "staging divides evenly");
     static_assert(RPP % 32 == 0 || 32 % RPP == 0, "rows per pass");
-    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int wm = wave / WGN, wn = wave % WGN;
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
 
@@ -201,7 +204,6 @@ __device__ __attribute__((always_inline)) inline void direct_acc(const DirectArg
     for (int i = 0; i < WBM; ++i)
 #pragma unroll
         for (int j = 0; j < WBN; ++j) acc[i][j] = (f32x16)0;
-    if (steps == 0) return;
     int s = 0;
     // The step is cut into GROUPS scheduling regions, one product of one 16-k
     // sub-step each; region x also splits its share of the next stage's pieces
@@ -235,8 +237,10 @@ __device__ __attribute__((always_inline)) inline void direct_acc(const DirectArg
             lds_barrier();
         }
     } else {
-        load_any(0);
-        stage(0);
+        if (steps > 0) {
+            load_any(0);
+            stage(0);
+        }
         if (steps > 1) load_any(1);
         lds_barrier();
     }
@@ -250,18 +254,63 @@ __device__ __attribute__((always_inline)) inline void direct_acc(const DirectArg
         }
         lds_barrier();
     }
+    for (; s < barriers; ++s) lds_barrier();
+}
+
+// K range of group gi of G: whole KS stages, the same number for every group
+// but the last ones.
+template <int KS, int G>
+__device__ inline void group_range(int64_t kb, int64_t ke, int gi, int64_t &b, int64_t &e, int &barriers)
+{
+    const int64_t stages = (ke - kb + KS - 1) / KS;
+    barriers = (int)((stages + G - 1) / G);
+    b = min<int64_t>(ke, kb + (int64_t)gi * barriers * KS);
+    e = min<int64_t>(ke, b + (int64_t)barriers * KS);
+}
+
+// Adds the accumulators of groups 1 .. G - 1 to group 0's, in group order,
+// through LDS (G - 1 groups x BM x BN floats).  Begins and ends with a barrier.
+template <int G, int WAVES, int NB>
+__device__ __attribute__((always_inline)) inline void group_sum(f32x16 (&acc)[NB], int gi, int t, char *lds)
+{
+    if constexpr (G > 1) {
+        const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+        f32x4 *part = reinterpret_cast<f32x4 *>(lds);
+        lds_barrier();
+        if (gi > 0) {
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    part[((((gi - 1) * WAVES + wave) * NB + x) * 4 + r) * 64 + lane] =
+                        f32x4{acc[x][4 * r], acc[x][4 * r + 1], acc[x][4 * r + 2], acc[x][4 * r + 3]};
+        }
+        lds_barrier();
+        if (gi == 0) {
+#pragma unroll
+            for (int q = 0; q < G - 1; ++q)
+#pragma unroll
+                for (int x = 0; x < NB; ++x)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const f32x4 v = part[(((q * WAVES + wave) * NB + x) * 4 + r) * 64 + lane];
+                        acc[x][4 * r] += v.x, acc[x][4 * r + 1] += v.y, acc[x][4 * r + 2] += v.z, acc[x][4 * r + 3] += v.w;
+                    }
+        }
+        lds_barrier();
+    }
 }
 
 // C = acc (or C += acc) on tile (tm, tn).  32 x 32 accumulator layout:
 // register r of lane l holds row (r / 4) * 8 + (l / 32) * 4 + r % 4, column
 // l % 32 of the block.
 template <int BM, int BN, int WGM, int WGN>
-__device__ __attribute__((always_inline)) inline void direct_store(const DirectArgs &g, int tm, int tn,
+__device__ __attribute__((always_inline)) inline void direct_store(const DirectArgs &g, int tm, int tn, int t,
                                                                    const f32x16 (&acc)[BM / 32 / WGM][BN / 32 / WGN],
                                                                    bool accumulate)
 {
     constexpr int MB = BM / 32, NB = BN / 32, WBM = MB / WGM, WBN = NB / WGN;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int wm = wave / WGN, wn = wave % WGN;
 #pragma unroll
     for (int i = 0; i < WBM; ++i)
@@ -281,7 +330,7 @@ __device__ __attribute__((always_inline)) inline void direct_store(const DirectA
 }
 
 struct DirectProbeLds {
-    double part[PROBE_NW][PS * PS];
+    double part[16][PS * PS];  // one row per wavefront
     float c[PS * PS];
     int marked;
 };
@@ -293,10 +342,10 @@ struct DirectProbeLds {
 // column's values, which is where probe_pick clamps to.)
 template <int BM, int BN, int WGM, int WGN>
 __device__ __attribute__((always_inline)) inline void probe_samples(const f32x16 (&acc)[BM / 32 / WGM][BN / 32 / WGN],
-                                                                    int r8, int c8, float *cs)
+                                                                    int t, int r8, int c8, float *cs)
 {
     constexpr int WBM = BM / 32 / WGM, WBN = BN / 32 / WGN;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int bi = r8 / 4 - wave / WGN * WBM, bj = c8 / 4 - wave % WGN * WBN;  // block within this wavefront's
 #pragma unroll
     for (int i = 0; i < WBM; ++i)
@@ -311,75 +360,82 @@ __device__ __attribute__((always_inline)) inline void probe_samples(const f32x16
 }
 
 // probe_tile's decision and record for one tile, from the float32 operands
-// themselves.  A thread takes every (32 x wavefronts)-th k and half of the
-// samples: every sampled row, and columns 4 h .. 4 h + 3 with h its half of
-// the wavefront, so that 32 lanes read 128 consecutive bytes of each sampled
-// row of A and one 16-byte piece each of 32 rows of B (each row of B is a
-// line of its own: the reads of B set the time).  The tile has just streamed
-// the same operands, so these reads hit the L2.  L.c holds the samples of C
-// (probe_samples): the tile's stores of C need not have finished.
+// themselves and on the float64 matrix cores: one v_mfma_f64_16x16x4_f64 takes
+// eight k at once, rows and columns 0-7 holding the sampled rows and columns
+// at k .. k + 3, rows and columns 8-15 the same ones at k + 4 .. k + 7; the two
+// diagonal 8 x 8 blocks of its result are the two halves of the 64 samples'
+// sums.  Operand lane l: row (column) l % 16, k l / 16; result register r of
+// lane l: row 4 r + l / 16, column l % 16.  Every sampled element is loaded
+// once (eight 32-byte pieces per load), and the sums need 8 registers and no
+// exchange but the last one: with one float64 accumulator per sample in
+// vector registers instead (64 of them a thread, then a butterfly over the
+// wavefront) the probe took 10 us of a 15 us call at LEN = 64.  The tile has
+// just streamed the same operands, so these reads hit the L2.  L.c holds the
+// samples of C (probe_samples): the tile's stores of C need not have finished.
 template <int THREADS>
 __device__ __attribute__((always_inline)) inline bool probe_direct(const DirectArgs &g, int bm, int bn, int64_t tile,
                                                                    int tm, int tn, double tau2,
                                                                    ProbeRecord *__restrict__ rec, DirectProbeLds &L)
 {
-    constexpr int WAVES = THREADS / 64;
-    constexpr int HC = PS / 2, KP = 32 * WAVES;
-    static_assert(PS == 8 && WAVES <= PROBE_NW, "8 x 8 samples, one per lane");
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    constexpr int WAVES = THREADS / 64, U = WAVES <= 4 ? 8 : 4;  // U steps of 8 k in flight per wavefront, twice
+    static_assert(PS == 8 && WAVES <= 16, "8 x 8 samples");
     const int64_t row0 = (int64_t)tm * bm, col0 = (int64_t)tn * bn;
     const int rext = (int)min<int64_t>(bm, g.M - row0), cext = (int)min<int64_t>(bn, g.N - col0);
-    const int q = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double acc[PS * HC];  // acc[4 u + j]: sample (u, 4 h + j)
+    const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kq = ((l & 15) >> 3) * 4 + (l >> 4);  // this lane's k within a step
+    const uint32_t offA = ((uint32_t)probe_pick(tile, l & 7, rext, 0) * (uint32_t)g.lda + kq) * 4u;
+    const uint32_t colB = (uint32_t)probe_pick(tile, l & 7, cext, 1);
+    const uint32_t offB = ((uint32_t)kq * (uint32_t)g.ldb + colB) * 4u;
+    const float *pA = g.A + row0 * g.lda, *pB = g.B + col0;
+    const uint32_t strideB = (uint32_t)(8 * WAVES * g.ldb * 4);  // bytes between a wavefront's steps
+    const int K = (int)g.K;
+    float xa[2][U], xb[2][U];
+    // U steps from k0 on, 8 WAVES apart; elements past K read the last one and
+    // count as zero
+    auto load = [&](int k0, float (&va)[U], float (&vb)[U]) {
+        if (k0 + (U - 1) * 8 * WAVES + 8 <= K) {
+            const auto ra = buffer_of(pA + k0), rb = buffer_of(pB + k0 * g.ldb);
 #pragma unroll
-    for (int z = 0; z < PS * HC; ++z) acc[z] = 0.0;
-    const float *a[PS];
-#pragma unroll
-    for (int u = 0; u < PS; ++u) a[u] = g.A + (row0 + probe_pick(tile, u, rext, 0)) * g.lda;
-    const int c0 = probe_pick(tile, 0, cext, 1), ch = (q >> 5) * HC;
-    const bool whole = c0 + PS <= cext;  // uniform: eight columns in a row
-    const float *b = g.B + col0 + c0;
-    // D passes of 32 WAVES elements in flight: a pass is one memory round trip
-    constexpr int D = 2;
-    float xa[D][PS], xb[D][HC];
-    auto load = [&](int64_t k, float (&va)[PS], float (&vb)[HC]) {
-        if (k < g.K) {
-#pragma unroll
-            for (int u = 0; u < PS; ++u) va[u] = a[u][k];
-            const float *bk = b + k * g.ldb;
-            if (whole) {
-                const f32x4u v = *reinterpret_cast<const f32x4u *>(bk + ch);
-                vb[0] = v.x, vb[1] = v.y, vb[2] = v.z, vb[3] = v.w;
-            } else {
-#pragma unroll
-                for (int j = 0; j < HC; ++j) vb[j] = bk[min(ch + j, cext - 1 - c0)];
+            for (int u = 0; u < U; ++u) {
+                va[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, offA, u * 8 * WAVES * 4, 0));
+                vb[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, offB, u * strideB, 0));
             }
         } else {
 #pragma unroll
-            for (int u = 0; u < PS; ++u) va[u] = 0.0f;
-#pragma unroll
-            for (int j = 0; j < HC; ++j) vb[j] = 0.0f;
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * 8 * WAVES + kq, kc = min(k, K - 1);
+                const float x = pA[(int64_t)(offA / 4u - kq) + kc], y = pB[(int64_t)kc * g.ldb + colB];
+                va[u] = k < K ? x : 0.0f;
+                vb[u] = k < K ? y : 0.0f;
+            }
         }
     };
-    const int64_t k0 = wave * 32 + (q & 31);
+    f64x4 d = {0.0, 0.0, 0.0, 0.0};
+    auto sum = [&](const float (&va)[U], const float (&vb)[U]) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) load(k0 + d * KP, xa[d], xb[d]);
-    for (int64_t k = 0; k < g.K; k += D * KP) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            double db[HC];
-#pragma unroll
-            for (int j = 0; j < HC; ++j) db[j] = xb[d][j];
-#pragma unroll
-            for (int u = 0; u < PS; ++u) {
-                const double da = xa[d][u];
-#pragma unroll
-                for (int j = 0; j < HC; ++j) acc[HC * u + j] = __builtin_fma(da, db[j], acc[HC * u + j]);
-            }
-            load(k0 + k + (D + d) * KP, xa[d], xb[d]);
-        }
+        for (int u = 0; u < U; ++u)
+            d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)va[u], (double)vb[u], d, 0, 0, 0);
+    };
+    constexpr int STEP = U * 8 * WAVES;
+    if (wave * 8 < K) load(wave * 8, xa[0], xb[0]);
+    for (int k0 = wave * 8; k0 < K; k0 += 2 * STEP) {
+        if (k0 + STEP < K) load(k0 + STEP, xa[1], xb[1]);
+        sum(xa[0], xb[0]);
+        if (k0 + 2 * STEP < K) load(k0 + 2 * STEP, xa[0], xb[0]);
+        if (k0 + STEP < K) sum(xa[1], xb[1]);
     }
-    return probe_finish<WAVES>(acc, (q & 31) / HC, ch + q % HC, L.c, g.C, g.ldc, row0, col0, rext, cext, tile, tau2,
-                               rec, L.part, &L.marked);
+    // lane l, column c: the sums of samples (l / 16, c % 8) and (l / 16 + 4,
+    // c % 8) over its block's half of the k
+    const bool hi = (l & 8) != 0;
+    double s0 = hi ? d[2] : d[0], s1 = hi ? d[3] : d[1];
+    s0 += __shfl_xor(s0, 8, 64);
+    s1 += __shfl_xor(s1, 8, 64);
+    if (!hi) {
+        L.part[wave][(l >> 4) * PS + (l & 7)] = s0;
+        L.part[wave][((l >> 4) + 4) * PS + (l & 7)] = s1;
+    }
+    return probe_decide<WAVES>(L.part, L.c, g.C, g.ldc, row0, col0, rext, cext, tile, tau2, rec, &L.marked);
 }
 
 }  // namespace dev

@@ -179,6 +179,19 @@ hipError_t launch_gemm_i8_auto(const void *pa1, const void *pb1, const void *pa4
                                const SplitK &sk = SplitK());
 hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t s);
 
+// ---- float32 straight from the operands (gemm_direct.hip) ------------------
+// C = A B in one launch with no packed operands, on 64 x 64 or 128 x 128
+// tiles (tile); products as above (6, 5 or 3).  rec non-null: the AUTO steps
+// (three products, float64 probe of each tile with threshold tau into rec,
+// correction of the marked ones) in the same launch.  sk.parts > 1: the K
+// range in that many workgroups per tile, with split_k_bytes(tile, ...) of
+// workspace.  lda and ldb at most DIRECT_MAX_LD (32-bit offsets in a tile).
+constexpr int64_t DIRECT_MAX_LD = (int64_t)1 << 19;
+hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
+                              double tau, ProbeRecord *rec, hipStream_t s, const SplitK &sk = SplitK());
+// Rows and columns of a tile configuration (0: the size heuristic's).
+void tile_dims(int tile, int64_t m, int64_t n, int &bm, int &bn);
+
 // ---- measurement kernels (onbox.hip) ---------------------------------------
 // Matrix instructions only (kind 0: bf16 32x32x16, 1: int8 32x32x32) on
 // every CU; *ops = the operations the launch performs.

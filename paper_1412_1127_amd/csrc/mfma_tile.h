@@ -910,34 +910,28 @@ template <int O, int C> __device__ __attribute__((always_inline)) inline void pr
     }
 }
 
-// The last step of a tile's probe, by a workgroup of WAVES wavefronts: acc
-// holds this thread's partial float64 sums of half of the samples, the lower
-// or the upper lanes' half; lane l ends with the sum in place l % 32 of its
-// half's, which is sample (u, v) of the tile.  Adds them up, compares with C (cs: the samples of C, in
+// The last step of a tile's probe, by a workgroup of WAVES wavefronts:
+// part[w] holds wavefront w's partial float64 sums of the samples (8 u + v).
+// Adds them up in wavefront order, compares with C (cs: the samples of C, in
 // LDS; NULL: read from C), decides, and writes the record (nullable).
-// Returns the decision in every thread.
+// Returns the decision in every thread.  Begins with a barrier.
 template <int WAVES>
-__device__ __attribute__((always_inline)) inline bool probe_finish(double (&acc)[PS * PS / 2], int u, int v,
-                                                                   const float *cs, const float *C, int64_t ldc, int64_t row0, int64_t col0, int rext,
-                                                                   int cext, int64_t tile, double tau2,
-                                                                   ProbeRecord *__restrict__ rec,
-                                                                   double (*part)[PS * PS], int *marked_out)
+__device__ __attribute__((always_inline)) inline bool probe_decide(const double (*part)[PS * PS], const float *cs,
+                                                                   const float *C, int64_t ldc, int64_t row0,
+                                                                   int64_t col0, int rext, int cext, int64_t tile,
+                                                                   double tau2, ProbeRecord *__restrict__ rec,
+                                                                   int *marked_out)
 {
-    constexpr int HS = PS * PS / 2;
-    const int q = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // butterfly over the half-wavefront; lane l ends with acc[0] = the
-    // wavefront's sum for sample l
-    probe_fold<16, HS>(acc, q);
-    part[wave][q] = acc[0];
     lds_barrier();
     // wavefront 0, one sample per lane: compare, then sum the squares over
     // the wavefront (a fixed butterfly: every lane ends with the same sums)
     if (threadIdx.x < 64) {
+        const int q = threadIdx.x, u = q / PS, v = q % PS;
         const int64_t row = row0 + probe_pick(tile, u, rext, 0), col = col0 + probe_pick(tile, v, cext, 1);
         double ref = part[0][q];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) ref += part[w][q];
-        const double c = cs ? (double)cs[PS * u + v] : (double)C[row * ldc + col];
+        const double c = cs ? (double)cs[q] : (double)C[row * ldc + col];
         double e2 = (c - ref) * (c - ref), r2 = ref * ref;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
@@ -946,7 +940,7 @@ __device__ __attribute__((always_inline)) inline bool probe_finish(double (&acc)
         }
         const int marked = (r2 > 0.0) ? (e2 > tau2 * r2) : (e2 > 0.0);
         if (rec) {
-            rec->ref[PS * u + v] = ref;
+            rec->ref[q] = ref;
             if (q < PS) {
                 rec->rows[q] = (int32_t)(row0 + probe_pick(tile, q, rext, 0));
                 rec->cols[q] = (int32_t)(col0 + probe_pick(tile, q, cext, 1));
@@ -1098,8 +1092,11 @@ __device__ __attribute__((always_inline)) inline bool probe_tile(const char *__r
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     }
-    return probe_finish<WAVES>(acc, q / PS, q % PS, nullptr, C, ldc, row0, col0, rext, cext, tile, tau2, rec, L.part,
-                               &L.marked);
+    // butterfly over the half-wavefront; lane l ends with acc[0] = the
+    // wavefront's sum for sample l
+    probe_fold<16, HS>(acc, q);
+    L.part[wave][q] = acc[0];
+    return probe_decide<WAVES>(L.part, nullptr, C, ldc, row0, col0, rext, cext, tile, tau2, rec, &L.marked);
 }
 
 }  // namespace dev

@@ -536,6 +536,53 @@ int resolve_tile(int t, const GemmShape &sh, uint32_t flags, int limbs)
     return it == tab.end() ? 0 : it->second.tile;
 }
 
+// The direct path's plan (launch_gemm_direct: no prepass, one launch) for a
+// float32 call whose tile the caller left open and no table entry fixes; tile
+// 0: the packed path.  The direct tile splits and loads its operands itself,
+// so it pays while its tiles come in one round of workgroups (one per CU), or
+// little more: measured, us per call, packed against direct, AUTO: LEN = 256
+// 18.4 / 9.2, 1000 40 / 19, 1531 73 / 44, 2048 98 / 68, 3072 (2.3 rounds of
+// 128 x 128) 294 / 252, 3500 (3.1 rounds) 390 / 402; six products: 256 10.8 /
+// 7.5, 1000 31 / 21, 2048 109 / 98, 2200 (1.3 rounds) 176 / 181.  Beyond one
+// round the packed path's larger tiles win: 4096 x 4096 x 512 75 / 87.
+// Among 64 x 64 tiles, 128 x 128 tiles and K parts the estimate below picks:
+// a base (launch, first loads, probe, stores) and a time per k and round, both
+// fitted to those runs, and for parts the ticket launch and the partial sums.
+struct DirectChoice {
+    int tile = 0, parts = 1;
+};
+
+DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
+{
+    DirectChoice best;
+    if (is_plain(flags) || is_f32mm(flags) || sh.m == 0 || sh.n == 0) return best;
+    const uint32_t prec = flags & ACC_PREC_MASK;
+    const uint32_t f = prec == ACC_PREC_AUTO ? (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3 : flags;
+    if (resolve_tile(ACC_FLOAT32, sh, f, 0)) return best;
+    const bool three = prec == ACC_PREC_AUTO || prec == ACC_PREC_CHEAP3;
+    const int64_t cus = accx::device_cu_count();
+    const int64_t t128 = ((sh.m + 127) / 128) * ((sh.n + 127) / 128), t64 = ((sh.m + 63) / 64) * ((sh.n + 63) / 64);
+    if (2 * t128 > (three ? 5 : 2) * cus) return best;
+    double best_us = 1e300;
+    for (int tile : {accx::GEMM_TILE_64, accx::GEMM_TILE_128}) {
+        const bool small = tile == accx::GEMM_TILE_64;
+        const int64_t tiles = small ? t64 : t128;
+        const double base = small ? (three ? 7.0 : 5.5) : (three ? 9.5 : 8.5);
+        const double per_k = small ? (three ? 0.0127 : 0.0165) : (three ? 0.0296 : 0.045);
+        for (int parts = 1; parts <= 8; ++parts) {
+            if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256)) break;
+            const double rounds = (double)((tiles * parts + cus - 1) / cus);
+            const double us = base + rounds * per_k * (double)sh.k / parts + (parts > 1 ? 5.0 + parts : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                best.tile = tile;
+                best.parts = parts;
+            }
+        }
+    }
+    return best;
+}
+
 // The split area if the caller's workspace holds it, else no split (a
 // workspace sized before the tile table changed).
 accx::SplitK split_for(int t, const GemmShape &sh, uint32_t flags, char *work, size_t work_bytes)
@@ -575,7 +622,7 @@ hipError_t cheap_pass(const char *pa, const char *pbt, float *c, const GemmShape
 acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmShape &sh, uint32_t flags, char *work,
                          size_t work_bytes, hipStream_t s, const CoReduce *red = nullptr)
 {
-    const accx::SplitK sk = split_for(ACC_FLOAT32, sh, flags, work, work_bytes);
+    accx::SplitK sk = split_for(ACC_FLOAT32, sh, flags, work, work_bytes);
     if (is_f32mm(flags)) {
         char *pa = work, *pbt = work + accx::packed_bytes(sh.m, sh.k, 4, 1);
         hipError_t e = accx::launch_pack_f32_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s);
@@ -584,11 +631,25 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
             accx::launch_gemm_f32mm(pa, pbt, c, sh, resolve_tile(ACC_FLOAT32, sh, flags, 0), s, sk),
             "gemm (float32 matrix cores) launch");
     }
+    const DirectChoice dc = direct_choice(sh, flags);
+    const uint32_t prec = flags & ACC_PREC_MASK;
+    if (dc.tile && sh.lda <= accx::DIRECT_MAX_LD && sh.ldb <= accx::DIRECT_MAX_LD) {
+        accx::SplitK dk;
+        // the partial sums take the place of the packed operands
+        if (dc.parts > 1 && accx::split_k_bytes(dc.tile, sh.m, sh.n, dc.parts) <= packed_pair(sh, 2, 3)) {
+            dk.parts = dc.parts;
+            dk.work = work;
+        }
+        auto *rec = prec == ACC_PREC_AUTO ? reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh)) : nullptr;
+        return check_launch(accx::launch_gemm_direct(a, b, c, sh,
+                                                     prec == ACC_PREC_FULL6 ? 6 : prec == ACC_PREC_FIVE ? 5 : 3, dc.tile,
+                                                     probe_tau(), rec, s, dk),
+                            "gemm (bf16x3, direct) launch");
+    }
     const size_t pb = accx::packed_bytes(sh.m, sh.k, 2, 3);
     char *pa = work, *pbt = work + pb;
     hipError_t e = accx::launch_pack_bf16x3_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s);
     if (e != hipSuccess) return fail_hip(e, "pack (bf16x3) launch");
-    const uint32_t prec = flags & ACC_PREC_MASK;
     if (prec == ACC_PREC_AUTO) {
         // cheap pass, float64 probe per tile, then the three missing products
         // on the tiles the probe marked (the others exit at once).  The tile
@@ -596,7 +657,10 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
         // the layout of this tile, which must not be left to a default that
         // each launch would resolve on its own.
         int tile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
-        if (!tile) tile = accx::default_tile(sh.m, sh.n);
+        if (!tile) tile = dc.tile ? dc.tile : accx::default_tile(sh.m, sh.n);
+        // rows too long for the direct path: the same tile (the records'
+        // layout does not depend on leading dimensions), unsplit
+        if (dc.tile) sk = accx::SplitK();
         auto *rec = reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh));
         e = cheap_pass(pa, pbt, c, sh, tile, sk, red, s);
         accx::RedFinal fin;
@@ -1679,7 +1743,8 @@ acc_status probe_layout(const GemmShape &sh, uint32_t flags, size_t *offset_out,
     if (is_plain(flags) || (flags & ACC_PREC_MASK) != ACC_PREC_AUTO)
         return fail(ACC_ERR_INVALID_ARG, "the probe runs only for the tiled kernel with ACC_PREC_AUTO");
     if (sh.m == 0 || sh.n == 0) return fail(ACC_ERR_INVALID_ARG, "an empty result has no probe records");
-    const int tile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
+    int tile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
+    if (!tile) tile = direct_choice(sh, flags).tile;
     *offset_out = probe_offset(sh);
     *count_out = accx::probe_tiles(tile, sh.m, sh.n);
     return ACC_OK;
