@@ -421,8 +421,8 @@ ACCX_API acc_status accx_reduce_dev_noalloc(acc_dtype t, const void *dX, int64_t
  * otherwise it is 512.  Matmuls in a batch use the six-product bf16x3 split
  * (or ACC_PREC_AUTO's steps, ACC_BATCH_PREC_AUTO);
  * a matmul's result is bitwise that of accx_matmul_dev with ACC_PREC_FULL6
- * (ACC_PREC_AUTO) and the same tile, run unsplit (a workspace without the
- * split area).  Reductions are deterministic (fixed chunking, chunk-order
+ * (ACC_PREC_AUTO) and the same tile forced, run unsplit (a workspace without
+ * the split area).  Reductions are deterministic (fixed chunking, chunk-order
  * combine). */
 #define ACC_BATCH_MATMUL 0
 #define ACC_BATCH_REDUCE 1

@@ -143,6 +143,101 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
     }
 }
 
+// C += the three correction products on the listed tiles: a persistent grid
+// over (marked tile, 128 x 128 sub-tile, K part).  How many tiles are marked is
+// known on the device only, and a few marked tiles must still fill the chip,
+// so the K parts per sub-tile follow from the count: about four units per
+// workgroup.  Parts leave their sums in `partials`, the last one (the record's
+// ticket) adds them in part order to C; the result does not depend on the
+// list's order.  Before, every 64 x 64 sub-tile of C had a workgroup that read
+// its record and, if marked, ran the packed three-plane tile over all of K:
+// 1104 of them on the 768 slots of the chip in two unequal rounds, 0.74 ms on
+// the row-scaled LEN = 8192 inputs (69 of 1024 tiles marked, 222 GFLOP); now
+// 0.46 ms.  The split into three planes bounds it (88 vector instructions for
+// 12 matrix instructions of a wavefront and 16 k).
+struct CorrPlan {
+    ProbeRecord *rec;
+    int tiles_n;        // marked tiles per row of C
+    int subs_m, subs_n; // 128 x 128 sub-tiles of a marked tile
+    float *partials;
+    int64_t cap;        // sub-tile sums `partials` holds
+    int max_parts;
+};
+
+__global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan c, RedFinal fin)
+{
+    constexpr int BM = 128, KS = 16, NBLK = 4, WORDS = BM * BM;
+    __shared__ __attribute__((aligned(1024))) char lds[direct_lds_bytes<BM, BM, KS, 3, PL_CORR3>()];
+    __shared__ int last_part;
+    if (fin.result && blockIdx.x == 0) {
+        float *w4 = reinterpret_cast<float *>(lds);
+        float v = 0.0f;
+        for (int k = threadIdx.x; k < fin.parts; k += 256) v += __uint_as_float(fin.part[k]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if ((threadIdx.x & 63) == 0) w4[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) *fin.result = fin.init + ((w4[0] + w4[1]) + (w4[2] + w4[3]));
+        __syncthreads();
+    }
+    const int count = __builtin_amdgcn_readfirstlane(c.rec[0].count);
+    if (count == 0) return;
+    const int subs = c.subs_m * c.subs_n;
+    const int64_t S = (int64_t)count * subs;
+    int64_t parts = min<int64_t>(min<int64_t>(c.max_parts, g.K / 256), (4 * (int64_t)gridDim.x + S - 1) / S);
+    parts = min<int64_t>(parts, c.cap / S);
+    if (parts < 1) parts = 1;
+    const int64_t kpart = ((g.K + parts - 1) / parts + KS - 1) / KS * KS;
+    parts = (g.K + kpart - 1) / kpart;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int64_t u = blockIdx.x; u < S * parts; u += gridDim.x) {
+        const int64_t x = u / parts, part = u % parts;
+        const int sub = (int)(x % subs);
+        const int tile = __builtin_amdgcn_readfirstlane(c.rec[x / subs].mark);
+        const int tm = tile / c.tiles_n * c.subs_m + sub / c.subs_n, tn = tile % c.tiles_n * c.subs_n + sub % c.subs_n;
+        if ((int64_t)tm * BM >= g.M || (int64_t)tn * BM >= g.N) continue;
+        f32x16 acc[2][2];
+        direct_acc<BM, BM, KS, 2, 2, 3, PL_CORR3>(g, tm, tn, part * kpart, min<int64_t>(g.K, (part + 1) * kpart),
+                                                  threadIdx.x, 0, lds, acc);
+        if (parts > 1) {
+            float *mine = c.partials + u * WORDS + wave * (NBLK * 1024) + lane;
+#pragma unroll
+            for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    __hip_atomic_store(mine + q * 1024 + r * 64, acc[q / 2][q % 2][r], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm<0>());
+            asm volatile("" ::: "memory");
+            __syncthreads();
+            if (threadIdx.x == 0)
+                last_part = ((atomicAdd(&c.rec[tile].ticket, 1u << (8 * sub)) >> (8 * sub)) & 255u) ==
+                            (uint32_t)(parts - 1);
+            __syncthreads();
+            const int last = last_part;
+            __syncthreads();  // read by all before the next unit writes it
+            if (!last) continue;
+            const float *p = c.partials + x * parts * WORDS + wave * (NBLK * 1024) + lane;
+#pragma unroll
+            for (int q = 0; q < NBLK; ++q) {
+                f32x16 sum = (f32x16)0;
+                for (int64_t d = 0; d < parts; ++d) {
+                    float w[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        w[r] = __hip_atomic_load(p + d * WORDS + q * 1024 + r * 64, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[r] += w[r];
+                }
+                acc[q / 2][q % 2] = sum;
+            }
+        }
+        direct_store<BM, BM, 2, 2>(g, tm, tn, threadIdx.x, acc, true);
+    }
+}
+
 template <int BM, int BN, int KS, int G, int NPROD, uint64_t PL, bool AUTO, int KSC = KS, int GC = G>
 hipError_t launch(const DirectArgs &g, const DirectPlan &pl, hipStream_t s)
 {
@@ -152,6 +247,21 @@ hipError_t launch(const DirectArgs &g, const DirectPlan &pl, hipStream_t s)
 }
 
 }  // namespace
+
+hipError_t launch_correction(const float *a, const float *b, float *c, const GemmShape &sh, int tile, ProbeRecord *rec,
+                             void *work, size_t work_bytes, int max_parts, hipStream_t s, const RedFinal &fin)
+{
+    int bm, bn;
+    tile_dims(tile, sh.m, sh.n, bm, bn);
+    if (bm % 128 || bn % 128) return hipErrorInvalidValue;
+    const DirectArgs g{a, b, c, sh.m, sh.n, sh.k, sh.lda, sh.ldb, sh.ldc};
+    const CorrPlan p{rec, (int)((sh.n + bn - 1) / bn), bm / 128, bn / 128, static_cast<float *>(work),
+                     (int64_t)(work_bytes / (128 * 128 * 4)), std::min(max_parts, 255)};
+    tmark("gemm_bf16x3_corr", s, true);
+    hipLaunchKernelGGL(correct_direct, dim3((unsigned)(2 * device_cu_count())), dim3(256), 0, s, g, p, fin);
+    tmark("gemm_bf16x3_corr", s, false);
+    return hipGetLastError();
+}
 
 hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
                               double tau, ProbeRecord *rec, hipStream_t s, const SplitK &sk)

@@ -313,9 +313,11 @@ __global__ __launch_bounds__(256) void pack_bf16x3_t(const float *__restrict__ X
 // (gbx per K tile).
 __global__ __launch_bounds__(256) void pack_bf16x3_pair(const float *__restrict__ A, int64_t M, int64_t lda,
                                                         char *__restrict__ pa, const float *__restrict__ B, int64_t N,
-                                                        int64_t ldb, char *__restrict__ pb, int64_t K, int ga, int gbx)
+                                                        int64_t ldb, char *__restrict__ pb, int64_t K, int ga, int gbx,
+                                                        uint32_t *zero)
 {
     __shared__ __attribute__((aligned(16))) uint32_t t[TP_ROWS][TP_COLS];
+    if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0u;
     const int64_t nkb = (K + 31) / 32;
     if ((int)blockIdx.x < ga) {
         pack_bf16x3_range<false>(A, M, K, lda, pa, (M + 31) / 32, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
@@ -621,6 +623,8 @@ __global__ __launch_bounds__(512) void gemm_i8_auto256(GemmArgs g, GemmArgs gm, 
 // with 512 threads, records written for the correction launch.
 constexpr int PROBE_THREADS = 512;
 
+// list: append the marked tiles to the records' list (its count zeroed
+// before).
 // fin (optional): a co-scheduled reduction's per-workgroup partials, which
 // workgroup 0 adds (index order, fixed tree) into *fin.result = fin.init +
 // sum once its tile is probed -- the reduction's last step rides in this
@@ -628,12 +632,15 @@ constexpr int PROBE_THREADS = 512;
 __global__ __launch_bounds__(PROBE_THREADS) void probe_f64(const char *__restrict__ pa, const char *__restrict__ pb,
                                                            const float *__restrict__ C, GemmShape sh, int bm, int bn,
                                                            int tiles_n, int64_t nkb, double tau2,
-                                                           ProbeRecord *__restrict__ rec, RedFinal fin)
+                                                           ProbeRecord *__restrict__ rec, int list,
+                                                           RedFinal fin)
 {
     __shared__ __attribute__((aligned(16))) ProbeLds L;
     const int64_t tile = blockIdx.x;
-    probe_tile<PROBE_THREADS>(pa, pb, C, sh.m, sh.n, sh.k, sh.ldc, bm, bn, tile, (int)(tile / tiles_n),
-                              (int)(tile % tiles_n), nkb, tau2, rec + tile, L);
+    if (probe_tile<PROBE_THREADS>(pa, pb, C, sh.m, sh.n, sh.k, sh.ldc, bm, bn, tile, (int)(tile / tiles_n),
+                                  (int)(tile % tiles_n), nkb, tau2, rec + tile, L) &&
+        list && threadIdx.x == 0)
+        rec[atomicAdd(&rec[0].count, 1u)].mark = (int32_t)tile;
     if (fin.result && blockIdx.x == 0) {
         __shared__ float w8[PROBE_THREADS / 64];
         float t = 0.0f;
@@ -845,14 +852,15 @@ hipError_t launch_pack_i8(const int32_t *x, int64_t rows, int64_t k, int64_t ld,
 }
 
 hipError_t launch_pack_bf16x3_pair(const float *a, int64_t m, int64_t lda, const float *b, int64_t n, int64_t ldb,
-                                   int64_t k, void *pa, void *pb, hipStream_t s)
+                                   int64_t k, void *pa, void *pb, hipStream_t s, uint32_t *zero)
 {
     const int64_t nkb = cdiv(k, 32), ua = cdiv(m, 32) * nkb;
     const int64_t ga = ua > 0 ? pack_grid(ua) : 0, gbx = cdiv(n, TP_COLS), gb = gbx * BF_SPLIT * nkb;
     if (ga + gb == 0) return hipSuccess;
     tmark("pack_bf16x3", s, true);
     hipLaunchKernelGGL(pack_bf16x3_pair, dim3((unsigned)(ga + gb)), dim3(256), 0, s, a, m, lda,
-                       static_cast<char *>(pa), b, n, ldb, static_cast<char *>(pb), k, (int)ga, (int)std::max<int64_t>(gbx, 1));
+                       static_cast<char *>(pa), b, n, ldb, static_cast<char *>(pb), k, (int)ga, (int)std::max<int64_t>(gbx, 1),
+                       zero);
     tmark("pack_bf16x3", s, false);
     return hipGetLastError();
 }
@@ -924,7 +932,7 @@ void tile_dims(int tile, int64_t m, int64_t n, int &bm, int &bn)
 }
 
 hipError_t launch_probe_f64(const void *pa, const void *pb, const float *c, const GemmShape &sh, int tile, double tau,
-                            ProbeRecord *rec, hipStream_t s, const RedFinal &fin)
+                            ProbeRecord *rec, bool list, hipStream_t s, const RedFinal &fin)
 {
     int bm, bn;
     tile_dims(tile, sh.m, sh.n, bm, bn);
@@ -932,7 +940,7 @@ hipError_t launch_probe_f64(const void *pa, const void *pb, const float *c, cons
     if (tiles_m * tiles_n == 0) return hipSuccess;
     tmark("probe_f64", s, true);
     hipLaunchKernelGGL(probe_f64, dim3((unsigned)(tiles_m * tiles_n)), dim3(PROBE_THREADS), 0, s, static_cast<const char *>(pa),
-                       static_cast<const char *>(pb), c, sh, bm, bn, tiles_n, cdiv(sh.k * 2, 64), tau * tau, rec, fin);
+                       static_cast<const char *>(pb), c, sh, bm, bn, tiles_n, cdiv(sh.k * 2, 64), tau * tau, rec, list ? 1 : 0, fin);
     tmark("probe_f64", s, false);
     return hipGetLastError();
 }

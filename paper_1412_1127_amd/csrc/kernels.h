@@ -77,8 +77,9 @@ hipError_t launch_pack_i8(const int32_t *x, int64_t rows, int64_t k, int64_t ld,
 // 64-bit words (stamp << 32 | max) that need no clearing between calls: each
 // call passes a fresh nonzero stamp, and a word with another stamp reads as
 // no maximum above 127 recorded.
+// zero (nullable): a word the float32 launch sets to zero.
 hipError_t launch_pack_bf16x3_pair(const float *a, int64_t m, int64_t lda, const float *b, int64_t n, int64_t ldb,
-                                   int64_t k, void *pa, void *pb, hipStream_t s);
+                                   int64_t k, void *pa, void *pb, hipStream_t s, uint32_t *zero = nullptr);
 // decide (optional, int8): the two max|x| words of a finished one-digit
 // pass with stamp `stamp`; the launch then packs only if more than one digit
 // is needed, and writes as many digit planes as are needed into units of
@@ -100,7 +101,12 @@ struct ProbeRecord {
     double ref[PROBE_SIDE * PROBE_SIDE];         // float64 dot products, ref[8*u + v] at (rows[u], cols[v])
     double err2, ref2;                           // sum over the samples of (C - ref)^2 and of ref^2
     int32_t corrected;                           // 1 if the tile got the three correction products
-    int32_t pad[3];
+    // The packed path's list of marked tiles, kept in the records: record 0's
+    // count (zeroed by the pack launch), record i's mark = the i-th marked
+    // tile's index (in any order), and per marked tile the K parts of its
+    // 128 x 128 sub-tiles that are done (8 bits each).
+    int32_t mark;
+    uint32_t count, ticket;
 };
 static_assert(sizeof(ProbeRecord) == 608, "probe record layout");
 
@@ -145,10 +151,11 @@ struct RedFinal {
     float *result = nullptr;
 };
 // Float64 probe of C per output tile of `tile`; tau: relative Frobenius
-// threshold above which a tile is marked for correction.  fin: a
+// threshold above which a tile is marked for correction.  list: append the
+// marked tiles to the records' list (count zeroed before).  fin: a
 // reduction's last step, run by the launch's first workgroup.
 hipError_t launch_probe_f64(const void *pa, const void *pb, const float *c, const GemmShape &sh, int tile, double tau,
-                            ProbeRecord *rec, hipStream_t s, const RedFinal &fin = RedFinal());
+                            ProbeRecord *rec, bool list, hipStream_t s, const RedFinal &fin = RedFinal());
 // Output tiles of `tile` (0 = the heuristic's choice) over an m x n result.
 int probe_tiles(int tile, int64_t m, int64_t n);
 // The configuration the size heuristic picks for an m x n result.
@@ -189,6 +196,14 @@ hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t s);
 constexpr int64_t DIRECT_MAX_LD = (int64_t)1 << 19;
 hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
                               double tau, ProbeRecord *rec, hipStream_t s, const SplitK &sk = SplitK());
+// The correction after a packed three-product pass and its probe: C += the
+// three missing products on the tiles in the records' list (rec: one record
+// per tile of `tile`, 128 x 128 or larger), straight from the float32 operands
+// (lda, ldb <= DIRECT_MAX_LD).  work: work_bytes for partial sums (256-byte
+// aligned) of at most max_parts K parts per sub-tile.  fin: a co-scheduled reduction's last step, run by workgroup 0.
+hipError_t launch_correction(const float *a, const float *b, float *c, const GemmShape &sh, int tile, ProbeRecord *rec,
+                             void *work, size_t work_bytes, int max_parts, hipStream_t s,
+                             const RedFinal &fin = RedFinal());
 // Rows and columns of a tile configuration (0: the size heuristic's).
 void tile_dims(int tile, int64_t m, int64_t n, int &bm, int &bn);
 

@@ -949,7 +949,7 @@ __device__ __attribute__((always_inline)) inline bool probe_decide(const double 
                 rec->err2 = e2;
                 rec->ref2 = r2;
                 rec->corrected = marked;
-                rec->pad[0] = rec->pad[1] = rec->pad[2] = 0;
+                rec->ticket = 0;  // mark and count belong to the list of marked tiles
             }
         }
         if (q == 0) *marked_out = marked;

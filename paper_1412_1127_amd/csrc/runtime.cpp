@@ -648,30 +648,38 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     }
     const size_t pb = accx::packed_bytes(sh.m, sh.k, 2, 3);
     char *pa = work, *pbt = work + pb;
-    hipError_t e = accx::launch_pack_bf16x3_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s);
+    auto *rec = reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh));
+    // the correction from the float32 operands, over the probe's list of
+    // marked tiles; else the packed one, which looks at every tile's record
+    int ptile = 0;
+    bool listed = false;
+    if (prec == ACC_PREC_AUTO) {
+        // The tile is made concrete here: the correction reads the probe's
+        // records in the layout of this tile, which must not be left to a
+        // default that each launch would resolve on its own.
+        ptile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
+        if (!ptile) ptile = dc.tile ? dc.tile : accx::default_tile(sh.m, sh.n);
+        listed = ptile != accx::GEMM_TILE_64 && sh.k > 0 && sh.lda <= accx::DIRECT_MAX_LD && sh.ldb <= accx::DIRECT_MAX_LD;
+    }
+    hipError_t e = accx::launch_pack_bf16x3_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s,
+                                                 listed ? &rec->count : nullptr);
     if (e != hipSuccess) return fail_hip(e, "pack (bf16x3) launch");
     if (prec == ACC_PREC_AUTO) {
         // cheap pass, float64 probe per tile, then the three missing products
-        // on the tiles the probe marked (the others exit at once).  The tile
-        // is made concrete here: the correction reads the probe's records in
-        // the layout of this tile, which must not be left to a default that
-        // each launch would resolve on its own.
-        int tile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
-        if (!tile) tile = dc.tile ? dc.tile : accx::default_tile(sh.m, sh.n);
-        // rows too long for the direct path: the same tile (the records'
-        // layout does not depend on leading dimensions), unsplit
+        // on the tiles the probe marked.
+        // Rows too long for the direct path: its tile (the records' layout
+        // does not depend on leading dimensions), unsplit.
         if (dc.tile) sk = accx::SplitK();
-        auto *rec = reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh));
-        e = cheap_pass(pa, pbt, c, sh, tile, sk, red, s);
+        e = cheap_pass(pa, pbt, c, sh, ptile, sk, red, s);
         accx::RedFinal fin;
         if (red) fin = accx::RedFinal{red->part, red->parts, red->init, red->result};
-        if (e == hipSuccess) e = accx::launch_probe_f64(pa, pbt, c, sh, tile, probe_tau(), rec, s, fin);
-        // the correction runs on 64 x 64 tiles, so a marked tile costs its
-        // share of the work, not a whole pass of the big tile (128 x 128
-        // correction tiles measured slower on the row-scaled LEN=8192
-        // inputs: 0.89 against 0.77 ms)
+        if (e == hipSuccess) e = accx::launch_probe_f64(pa, pbt, c, sh, ptile, probe_tau(), rec, listed, s, fin);
         if (e == hipSuccess)
-            e = accx::launch_gemm_bf16x3(pa, pbt, c, sh, -3, true, accx::GEMM_TILE_64, s, rec, accx::SplitK(), tile);
+            // (a forced tile is corrected in one K part: the sums of a batch)
+            e = listed ? accx::launch_correction(a, b, c, sh, ptile, rec, work, packed_pair(sh, 2, 3),
+                                                 (flags & ACC_TILE_MASK) ? 1 : 8, s)
+                       : accx::launch_gemm_bf16x3(pa, pbt, c, sh, -3, true, accx::GEMM_TILE_64, s, rec, accx::SplitK(),
+                                                  ptile);
         return check_launch(e, "gemm (bf16x3, probed) launch");
     }
     const int products = (prec == ACC_PREC_CHEAP3) ? 3 : (prec == ACC_PREC_FIVE) ? 5 : 6;
