@@ -25,6 +25,7 @@ SOURCES = [
     "reduce.hip",
     "gemm_mfma.hip",
     "gemm_direct.hip",
+    "gemm_i8_direct.hip",
     "batch.hip",
     "onbox.hip",
 ]

@@ -27,8 +27,6 @@ namespace dev {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-// float4 at any 4-byte address (rows of a view start anywhere)
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 struct DirectArgs {
     const float *A, *B;  // row-major M x K and K x N
@@ -38,9 +36,9 @@ struct DirectArgs {
 
 // A buffer resource over all 4 GB above p (uniform): offsets are checked by
 // the caller, not by the resource.
-__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const float *p)
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *p)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, 0xffffffff, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, 0xffffffff, 0x00020000);
 }
 
 // The planes of two elements, packed: w[p] = plane p of x0 (low half) and x1.

@@ -196,6 +196,11 @@ hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t s);
 constexpr int64_t DIRECT_MAX_LD = (int64_t)1 << 19;
 hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
                               double tau, ProbeRecord *rec, hipStream_t s, const SplitK &sk = SplitK());
+// int32: C = A B modulo 2^32 in one launch straight from the operands, with
+// as many int8 digits as each stage of the K loop needs (gemm_i8_direct.hip);
+// tile 64 x 64 or 128 x 128, sk, lda and ldb as above.
+hipError_t launch_gemm_i8_direct(const int32_t *a, const int32_t *b, int32_t *c, const GemmShape &sh, int tile,
+                                 hipStream_t s, const SplitK &sk = SplitK());
 // The correction after a packed three-product pass and its probe: C += the
 // three missing products on the tiles in the records' list (rec: one record
 // per tile of `tile`, 128 x 128 or larger), straight from the float32 operands

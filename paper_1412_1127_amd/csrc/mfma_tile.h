@@ -29,6 +29,11 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// 16 bytes at any 4-byte address (rows of a view start anywhere; the hardware
+// takes such loads)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int PLANE_BYTES = 2048;  // 32 rows x 64 bytes
 
@@ -80,10 +85,10 @@ __device__ __attribute__((always_inline)) inline void pack_bf16x3_range(const fl
         if (TRANS) {
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = (row < R && k0 + t < K) ? X[(k0 + t) * ld + row] : 0.0f;
-        } else if (row < R && k0 + 8 <= K && ((ld & 3) == 0) && (((uintptr_t)X & 15u) == 0)) {
-            const f32x4 *p = reinterpret_cast<const f32x4 *>(X + row * ld + k0);
+        } else if (row < R && k0 + 8 <= K) {
+            const f32x4u *p = reinterpret_cast<const f32x4u *>(X + row * ld + k0);
             // read once: non-temporal, so that the stream keeps out of the caches
-            const f32x4 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);
+            const f32x4u a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);
             v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
         } else {
 #pragma unroll
@@ -103,6 +108,32 @@ __device__ __attribute__((always_inline)) inline void pack_bf16x3_range(const fl
         *reinterpret_cast<u16x8 *>(u + PLANE_BYTES) = m;
         *reinterpret_cast<u16x8 *>(u + 2 * PLANE_BYTES) = l;
     }
+}
+
+// Digit 0 of four consecutive elements, packed into one word: the balanced
+// base-256 digit ((x + 128) mod 256) - 128 is the low byte of x read as int8.
+__device__ inline int low_bytes4(int32_t a, int32_t b, int32_t c, int32_t d)
+{
+    return (int)(((uint32_t)a & 255u) | (((uint32_t)b & 255u) << 8) | (((uint32_t)c & 255u) << 16) |
+                 ((uint32_t)d << 24));
+}
+
+// The four balanced base-256 digits of x as the bytes of a word: x +
+// 0x00808080 carries as the balanced digits do, and the lower three bytes are
+// then the digits plus 128.
+__device__ inline uint32_t digit_bytes(int32_t x) { return ((uint32_t)x + 0x00808080u) ^ 0x00808080u; }
+
+// Digit p of four elements into w[p], one byte each.
+__device__ inline void digits4(int32_t x0, int32_t x1, int32_t x2, int32_t x3, uint32_t (&w)[4])
+{
+    const uint32_t y0 = digit_bytes(x0), y1 = digit_bytes(x1), y2 = digit_bytes(x2), y3 = digit_bytes(x3);
+    // bytes 0-3 of the selector's range are the second operand's
+    const uint32_t a = __builtin_amdgcn_perm(y1, y0, 0x05010400u), b = __builtin_amdgcn_perm(y3, y2, 0x05010400u);
+    const uint32_t c = __builtin_amdgcn_perm(y1, y0, 0x07030602u), d = __builtin_amdgcn_perm(y3, y2, 0x07030602u);
+    w[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+    w[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    w[2] = __builtin_amdgcn_perm(d, c, 0x05040100u);
+    w[3] = __builtin_amdgcn_perm(d, c, 0x07060302u);
 }
 
 // ------------------------------------------------------------------- GEMM --

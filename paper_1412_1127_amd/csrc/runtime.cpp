@@ -583,6 +583,41 @@ DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
     return best;
 }
 
+// The same for an int32 call whose digit count is left open
+// (launch_gemm_i8_direct).  The values are not known here, so the direct path
+// is taken where it is the faster one on one-digit data, the packed path's
+// best case: us per call, packed against direct, values in [-16, 16] and (full
+// range): LEN = 256 15.3 / 7.1 (23 / 8.5), 512 16.1 / 9.9 (34 / 12.4), 1000
+// 18.2 / 16.6 (61 / 23), 1300 23.8 / 28 (88 / 41), 128 x 128 x 4096 20.6 /
+// 18.2 (133 / 23).  Both estimates are fitted to those runs.
+DirectChoice direct_choice_i32(const GemmShape &sh, uint32_t flags)
+{
+    DirectChoice best;
+    if (is_plain(flags) || flag_limbs(flags) || sh.m == 0 || sh.n == 0 || resolve_tile(ACC_INT32, sh, flags, 1))
+        return best;
+    const int64_t cus = accx::device_cu_count();
+    const double mnk = (double)sh.m * (double)sh.n * (double)sh.k;
+    const bool splits = split_plan(ACC_INT32, sh, flags).parts > 1;  // the packed path: a ticket launch more
+    double best_us =
+        0.95 * ((splits ? 18.0 : 14.0) + 5.0 * (double)(sh.m + sh.n) * (double)sh.k / 3.5e6 + 2.0 * mnk / 1.2e9);
+    for (int tile : {accx::GEMM_TILE_64, accx::GEMM_TILE_128}) {
+        const int64_t edge = tile == accx::GEMM_TILE_64 ? 64 : 128;
+        const int64_t tiles = ((sh.m + edge - 1) / edge) * ((sh.n + edge - 1) / edge);
+        if (tiles > cus) continue;
+        for (int parts = 1; parts <= 8; ++parts) {
+            if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256)) break;
+            const double us = (edge == 64 ? 4.8 : 5.5) + (edge == 64 ? 0.0115 : 0.0225) * (double)sh.k / parts +
+                              (parts > 1 ? 3.0 + 0.6 * parts : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                best.tile = tile;
+                best.parts = parts;
+            }
+        }
+    }
+    return best;
+}
+
 // The split area if the caller's workspace holds it, else no split (a
 // workspace sized before the tile table changed).
 accx::SplitK split_for(int t, const GemmShape &sh, uint32_t flags, char *work, size_t work_bytes)
@@ -706,6 +741,16 @@ uint32_t next_stamp()
 acc_status run_tiled_i32(const int32_t *a, const int32_t *b, int32_t *c, const GemmShape &sh, uint32_t flags,
                          char *work, size_t work_bytes, hipStream_t s)
 {
+    const DirectChoice dc = direct_choice_i32(sh, flags);
+    if (dc.tile && sh.lda <= accx::DIRECT_MAX_LD && sh.ldb <= accx::DIRECT_MAX_LD) {
+        accx::SplitK dk;
+        // the partial sums take the place of the packed operands
+        if (dc.parts > 1 && accx::split_k_bytes(dc.tile, sh.m, sh.n, dc.parts) <= packed_pair(sh, 1, 4)) {
+            dk.parts = dc.parts;
+            dk.work = work;
+        }
+        return check_launch(accx::launch_gemm_i8_direct(a, b, c, sh, dc.tile, s, dk), "gemm (int8, direct) launch");
+    }
     const accx::SplitK sk = split_for(ACC_INT32, sh, flags, work, work_bytes);
     uint64_t *maxabs = reinterpret_cast<uint64_t *>(work);
     char *pa = work + kMaxabsBytes;
