@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
         int64_t b, e;
         int barriers;
         group_range<KS, G>(p0, p1, gi, b, e, barriers);
-        direct_acc<BM, BN, KS, 2, 2, NPROD, PL>(
+        direct_acc<BM, BN, KS, 2, 2, NPROD, PL, (NPROD >= 5 && BM == 128)>(
             g, tm, tn, b, e, t, barriers, lds + gi * direct_lds_bytes<BM, BN, KS, NPROD, PL>(), acc.tile);
         group_sum<G, 4>(acc.flat, gi, t, lds);
     }

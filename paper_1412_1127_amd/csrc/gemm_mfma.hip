@@ -597,7 +597,7 @@ __global__ __launch_bounds__(512) void gemm_i8_auto256(GemmArgs g, GemmArgs gm, 
     if (nd > 1)
         gemm_i8_multi_body<4>(gm, nd, lds);
     else if ((int)blockIdx.x < grid1)
-        gemm_packed_body<true, 1, 256, 256, 64, 2, 4, 3, 1, PL_L1, 1, 1, false>(g, lds);
+        gemm_packed_body<true, 1, 256, 256, 64, 2, 4, 3, 1, PL_L1, 1, 3, false>(g, lds);
 }
 
 // ------------------------------------------------------- float64 probe --
@@ -645,8 +645,8 @@ __global__ __launch_bounds__(PROBE_THREADS) void probe_f64(const char *__restric
 // Tile configurations (BM x BN, wavefront grid, K-step bytes, ring depth):
 //  T256     256 x 256, 8 waves (2x4), 32 B (bf16x3) / 64 B (int8), 3 stages:
 //           one workgroup per CU, 144 / 96 KB LDS (bf16x3 with two planes:
-//           96 KB); first-product look-ahead (bf16x3), full look-ahead
-//           (one-digit int8).
+//           96 KB); alternating loop (with the co-scheduled sum:
+//           first-product look-ahead).
 //  T256x128 256 x 128, 4 waves (2x2), 32 B / 64 B, 2 stages: 72 / 48 KB LDS,
 //           two workgroups per CU that do not share barriers.
 //  T128     128 x 128, 4 waves (2x2), 32 B, 3 stages: 72 KB (bf16x3);
@@ -686,12 +686,7 @@ hipError_t run_gemm(int tile, const GemmArgs &g, hipStream_t s)
     constexpr int KS = P == 3 ? 32 : 64;  // K-step bytes of the big tiles
     switch (tile) {
     case GEMM_TILE_256:
-        // Look-ahead: full for the one-digit int8 tile (two fragment sets of
-        // 48 registers fit beside its 128 accumulator registers), first-product
-        // only for bf16x3, whose three planes leave no room for a second full
-        // set at two wavefronts per SIMD.  (A fourth stage, which fits for a
-        // two-plane pass, measured 4 % slower: the loads are not the limit.)
-        return launch_tile<INT8, P, 256, 256, KS, 2, 4, 3, NPROD, PL, NACC, INT8 ? 1 : 2>(g, s);
+        return launch_tile<INT8, P, 256, 256, KS, 2, 4, 3, NPROD, PL, NACC, 3>(g, s);
     case GEMM_TILE_256W4:
         // look-ahead for bf16x3 only: the int8 tile (two K sub-steps per
         // stage) would need more registers than a wavefront has

@@ -395,7 +395,8 @@ template <int THREADS, int NS> constexpr int red_lds_bytes() { return NS * THREA
 
 //
 // LAM selects the main loop: 0 plain (wait, barrier, read, compute), 1 full
-// look-ahead, 2 first-product look-ahead (described at its loop below).
+// look-ahead, 2 first-product look-ahead, 3 alternating (described at their
+// loops below).
 // Full look-ahead: each iteration waits for the NEXT stage, reads its
 // operand fragments from LDS into a second register set and runs the matrix
 // instructions of the current stage from registers, with the LDS reads
@@ -440,6 +441,7 @@ __device__ __attribute__((always_inline)) inline void gemm_tile(const GemmArgs &
     static_assert(LAM != 2 || (SUB == 1 && NPROD > 1), "first-product look-ahead: one matrix step per stage");
     static_assert(NS * STAGE <= 160 * 1024, "LDS");
     static_assert(NPL <= P, "product list names a plane the operand lacks");
+    static_assert(LAM != 3 || (NS == 3 && WAVES == 8 && WGM == 2), "alternating loop: two groups of four wavefronts");
     static_assert(!RED || (LAM == 2 && NS == 3 && !INT8), "co-scheduled reduction: first-product look-ahead, 3 stages");
 
     // wavefront index in a scalar register: everything derived from it
@@ -652,6 +654,82 @@ __device__ __attribute__((always_inline)) inline void gemm_tile(const GemmArgs &
                 for (int w = 0; w < WAVES; ++w) t += red_w[w];
                 g.red_part[blockIdx.x] = __float_as_uint(t);
             }
+        }
+    } else if constexpr (LAM == 3) {
+        // Alternating loop: the two wavefronts of a SIMD (w and w + 4: the two
+        // rows of wavefronts) take turns.  In each phase one group runs all
+        // matrix instructions of a step from registers while the other reads
+        // its next step's fragments from LDS and issues loads; a barrier ends
+        // the phase and the groups swap.  The matrix cores then wait for
+        // neither LDS nor the barrier's stragglers: the group whose turn it is
+        // has everything in registers.  Both groups run the same program, group
+        // 1 one phase later.  Stage s is read by group 0 in phase 2s - 1 and by
+        // group 1 in phase 2s, so the loads of stage s + 2 that each group
+        // issues while reading stage s refill a buffer both are done with, and
+        // stage s + 1 has to have arrived at the end of phase 2s.
+        // Measured on the 256 x 256 tile against the look-ahead loops, LEN =
+        // 4096 and 8192: one-digit int8 76.5 -> 70.0 us and 465 -> 449 us, six
+        // products 548 -> 539 and 4346 -> 4273 us (matrix cores busy 77 % of
+        // the cycles at 1.9 GHz), three products 330 -> 329 and 2286 -> 2270 us;
+        // with the co-scheduled sum beside the three products 401 -> 427 us,
+        // so that pass keeps the first-product look-ahead.
+        struct FragSet {
+            Frag a[SUB][NPL][WBM], b[SUB][NPL][WBN];
+        } F;
+        auto phase_end = [&] {
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // this wavefront's loads of stage s have arrived (those of s + 1 may be in flight)
+        auto arrived = [&](int s) {
+            if (s + 1 < nsteps)
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm<LPW>());
+            else
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm<0>());
+        };
+        if (nsteps > 0) {
+            arrived(0);
+            phase_end();
+            if (wm == 1) phase_end();
+            for (int step = 0; step < nsteps; ++step) {
+                const char *sA = lds + (step % NS) * STAGE;
+                const char *sB = sA + MB * LUNIT;
+#pragma unroll
+                for (int s = 0; s < SUB; ++s) {
+                    const int off = (2 * s + (lane >> 5)) * 512 + (lane & 31) * 16;
+#pragma unroll
+                    for (int p = 0; p < NPL; ++p) {
+#pragma unroll
+                        for (int i = 0; i < WBM; ++i)
+                            F.a[s][p][i] = *reinterpret_cast<const Frag *>(sA + (wm * WBM + i) * LUNIT + p * 32 * KBK + off);
+#pragma unroll
+                        for (int j = 0; j < WBN; ++j)
+                            F.b[s][p][j] = *reinterpret_cast<const Frag *>(sB + (wn * WBN + j) * LUNIT + p * 32 * KBK + off);
+                    }
+                }
+                if (step + 2 < nsteps) issue(step + 2);
+                __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0)
+                if (wm == 1) arrived(step + 1);
+                phase_end();
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int s = 0; s < SUB; ++s)
+#pragma unroll
+                    for (int t = 0; t < NPROD; ++t)
+#pragma unroll
+                        for (int i = 0; i < WBM; ++i)
+#pragma unroll
+                            for (int j = 0; j < WBN; ++j)
+                                acc[prod_acc(PL, t)][i][j] = M::run(F.a[s][prod_p(PL, t)][i], F.b[s][prod_q(PL, t)][j],
+                                                                    acc[prod_acc(PL, t)][i][j]);
+                __builtin_amdgcn_s_setprio(0);
+                if (wm == 0) arrived(step + 1);
+                phase_end();
+            }
+            if (wm == 0) phase_end();
         }
     } else if constexpr (LAM == 1) {
         struct FragSet {
