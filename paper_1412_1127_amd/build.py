@@ -23,6 +23,7 @@ SOURCES = [
     "serve.cpp",
     "matmul_plain.hip",
     "reduce.hip",
+    "reduce_one.hip",
     "gemm_mfma.hip",
     "gemm_direct.hip",
     "gemm_i8_direct.hip",

@@ -23,9 +23,9 @@ hipError_t launch_matmul_plain_i32(const int32_t *a, const int32_t *b, int32_t *
                                    bool listing1b_mapping, hipStream_t s);
 
 // ---- reduction(+) ----------------------------------------------------------
-// Fast: a streaming pass that stores one partial per block, then a
-// one-block launch that adds them in index order.
-// Workspace: 4 bytes per block (<= 4096 blocks), any contents.
+// Fast: a streaming pass that stores one partial per block, which the block
+// that arrives last, or a one-block launch, adds in index order.
+// Workspace: 4 bytes for each of 4096 blocks, any contents.
 size_t reduce_fast_workspace_bytes(int64_t n);
 // Plain: one element per thread and a block tree, then one block combines.
 size_t reduce_plain_workspace_bytes(int64_t n);

@@ -13,11 +13,10 @@
 //    eight independent 16-byte accumulators over a grid-stride slice, a
 //    wavefront reduces with cross-lane exchanges, the wavefronts of a
 //    workgroup combine through LDS, and each workgroup stores one partial.
-//    A second, one-workgroup launch adds the partials in index order and
-//    then the initial value.  (Electing the last workgroup with an atomic
-//    ticket instead saves that launch but needs a device-scope release in
-//    every workgroup, an L2 write-back on gfx950: measured 18 us slower over
-//    1 GiB than the two launches.)
+//    The partials are added in index order and then the initial value: by
+//    the workgroup whose partial arrives last if there are few of them (one
+//    launch, in which no workgroup waits for another), else by a second,
+//    one-workgroup launch.
 // Both are bitwise deterministic: nothing depends on the order in which
 // workgroups finish.
 //
@@ -28,47 +27,10 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
+#include "reduce_body.h"
 
 namespace accx {
 namespace {
-
-constexpr int RT = 256;          // threads per workgroup
-constexpr int RU = 8;            // 16-byte loads in flight per thread
-constexpr int MAX_BLOCKS = 4096; // fast kernel: upper bound on workgroups
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-template <typename L> struct Vec;
-template <> struct Vec<float> { using T = f4; };
-template <> struct Vec<uint32_t> { using T = u4; };
-
-template <typename L> __device__ inline L hsum(typename Vec<L>::T v) { return (v.x + v.y) + (v.z + v.w); }
-
-template <typename L> __device__ inline L wave_sum(L v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = v + __shfl_xor(v, o, 64);
-    return v;
-}
-
-// Sum over the 256 threads of a workgroup, fixed order; valid in thread 0.
-template <typename L> __device__ inline L block_sum(L v, L *lds4)
-{
-    v = wave_sum(v);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) lds4[w] = v;
-    __syncthreads();
-    L r = 0;
-    if (threadIdx.x == 0) r = (lds4[0] + lds4[1]) + (lds4[2] + lds4[3]);
-    return r;
-}
-
-__device__ inline uint32_t to_bits(float v) { return __float_as_uint(v); }
-__device__ inline uint32_t to_bits(uint32_t v) { return v; }
-template <typename L> __device__ inline L from_bits(uint32_t b);
-template <> __device__ inline float from_bits<float>(uint32_t b) { return __uint_as_float(b); }
-template <> __device__ inline uint32_t from_bits<uint32_t>(uint32_t b) { return b; }
 
 template <typename L>
 __global__ __launch_bounds__(RT) void reduce_fast(const L *__restrict__ x, int64_t n, uint32_t *__restrict__ partials)
@@ -154,110 +116,6 @@ __global__ __launch_bounds__(RT) void reduce_plain_final(const L *__restrict__ p
     }
     if (threadIdx.x == 0) result[0] = init + s[0];
 }
-
-// ---- reduction variables of any operator and type --------------------------
-//
-// Up to four reduction variables over one array in one pass (the SRAD loop
-// keeps a sum and a sum of squares of the same image): variable v combines
-// f_v(x[k]) with operator op_v, where f_v(x) = x or x*x in the element type.
-// Operators: + (integers wrap around), max, min (floats: a NaN operand is
-// ignored, as fmax/fmin do).  Each thread folds its grid-stride slice into
-// one accumulator per variable in a fixed order, the workgroup combines its
-// threads in a fixed tree and stores one partial per variable, and a second,
-// one-workgroup launch folds the partials in index order and then the
-// initial value: result_v = init_v (op_v) (partial_0 (op_v) partial_1 ...).
-
-template <typename E> struct Red;
-template <> struct Red<float> {
-    using V = f4;
-    using Bits = uint32_t;
-    static constexpr int W = 4;
-    __device__ static float lowest() { return -__builtin_inff(); }
-    __device__ static float highest() { return __builtin_inff(); }
-    __device__ static float add(float a, float b) { return a + b; }
-    __device__ static float mul(float a, float b) { return a * b; }
-    __device__ static float max(float a, float b) { return __builtin_fmaxf(a, b); }
-    __device__ static float min(float a, float b) { return __builtin_fminf(a, b); }
-    __device__ static bool nonzero(float a) { return a != 0.0f; }
-};
-typedef double d2 __attribute__((ext_vector_type(2)));
-template <> struct Red<double> {
-    using V = d2;
-    using Bits = uint64_t;
-    static constexpr int W = 2;
-    __device__ static double lowest() { return -__builtin_inf(); }
-    __device__ static double highest() { return __builtin_inf(); }
-    __device__ static double add(double a, double b) { return a + b; }
-    __device__ static double mul(double a, double b) { return a * b; }
-    __device__ static double max(double a, double b) { return __builtin_fmax(a, b); }
-    __device__ static double min(double a, double b) { return __builtin_fmin(a, b); }
-    __device__ static bool nonzero(double a) { return a != 0.0; }
-};
-typedef int32_t i4 __attribute__((ext_vector_type(4)));
-template <> struct Red<int32_t> {
-    using V = i4;
-    using Bits = uint32_t;
-    static constexpr int W = 4;
-    __device__ static int32_t lowest() { return INT32_MIN; }
-    __device__ static int32_t highest() { return INT32_MAX; }
-    __device__ static int32_t add(int32_t a, int32_t b) { return (int32_t)((uint32_t)a + (uint32_t)b); }
-    __device__ static int32_t mul(int32_t a, int32_t b) { return (int32_t)((uint32_t)a * (uint32_t)b); }
-    __device__ static int32_t max(int32_t a, int32_t b) { return a > b ? a : b; }
-    __device__ static int32_t min(int32_t a, int32_t b) { return a < b ? a : b; }
-    __device__ static bool nonzero(int32_t a) { return a != 0; }
-};
-typedef int64_t l2 __attribute__((ext_vector_type(2)));
-template <> struct Red<int64_t> {
-    using V = l2;
-    using Bits = uint64_t;
-    static constexpr int W = 2;
-    __device__ static int64_t lowest() { return INT64_MIN; }
-    __device__ static int64_t highest() { return INT64_MAX; }
-    __device__ static int64_t add(int64_t a, int64_t b) { return (int64_t)((uint64_t)a + (uint64_t)b); }
-    __device__ static int64_t mul(int64_t a, int64_t b) { return (int64_t)((uint64_t)a * (uint64_t)b); }
-    __device__ static int64_t max(int64_t a, int64_t b) { return a > b ? a : b; }
-    __device__ static int64_t min(int64_t a, int64_t b) { return a < b ? a : b; }
-    __device__ static bool nonzero(int64_t a) { return a != 0; }
-};
-
-template <typename E> __device__ inline E red_identity(int op)
-{
-    return op == RED_SUM ? (E)0 : op == RED_MAX ? Red<E>::lowest() : Red<E>::highest();
-}
-
-template <typename E> __device__ inline E red_apply(int op, E a, E b)
-{
-    return op == RED_SUM ? Red<E>::add(a, b) : op == RED_MAX ? Red<E>::max(a, b) : Red<E>::min(a, b);
-}
-
-template <typename E> __device__ inline E bits_as(uint64_t b)
-{
-    typename Red<E>::Bits t = (typename Red<E>::Bits)b;
-    return __builtin_bit_cast(E, t);
-}
-template <typename E> __device__ inline uint64_t as_bits(E v)
-{
-    return (uint64_t)__builtin_bit_cast(typename Red<E>::Bits, v);
-}
-
-// Combine v over the workgroup in a fixed order; valid in thread 0.
-template <typename E> __device__ inline E block_apply(int op, E v, E *lds4)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = red_apply<E>(op, v, __shfl_xor(v, o, 64));
-    if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = v;
-    __syncthreads();
-    E r = v;
-    if (threadIdx.x == 0) r = red_apply<E>(op, red_apply<E>(op, lds4[0], lds4[1]), red_apply<E>(op, lds4[2], lds4[3]));
-    __syncthreads();
-    return r;
-}
-
-// Operators fixed at compile time: SIG holds (op | square << 2) of variable v
-// in bits 4v..4v+3; SIG_RUNTIME reads them from `vars` (any combination, but
-// the per-element operator selection then costs more VALU work than the
-// element's load: about 4.5 instead of 6.9 TB/s over 1 GiB).
-constexpr uint32_t SIG_RUNTIME = 0xffffffffu;
 
 template <typename E, int NV, uint32_t SIG>
 __global__ __launch_bounds__(RT) void reduce_vars(const E *__restrict__ x, int64_t n, RedVars vars,
@@ -413,7 +271,12 @@ hipError_t launch_reduce(const L *x, int64_t n, L init, L *result, void *work, b
     } else {
         const int64_t g = fast_blocks(n);
         uint32_t *partials = static_cast<uint32_t *>(work);
-        tmark("reduce_fast", s, true);  // both launches
+        tmark("reduce_fast", s, true);  // one launch or both
+        if (reduce_in_one_launch(g, s)) {
+            launch_reduce_one(x, n, init, result, partials, (unsigned)g, s);
+            tmark("reduce_fast", s, false);
+            return hipGetLastError();
+        }
         hipLaunchKernelGGL(reduce_fast<L>, dim3((unsigned)g), dim3(RT), 0, s, x, n, partials);
         hipLaunchKernelGGL(reduce_fast_final<L>, dim3(1), dim3(RT), 0, s, partials, (unsigned)g, init, result);
         tmark("reduce_fast", s, false);
@@ -477,7 +340,12 @@ hipError_t launch_vars(const E *x, int64_t n, const RedVars &vars, E *result, vo
     }
     const int64_t g = fast_blocks(n * (int64_t)sizeof(E) / 4);
     uint64_t *partials = static_cast<uint64_t *>(work);
-    tmark("reduce_vars", s, true);  // both launches
+    tmark("reduce_vars", s, true);  // one launch or both
+    if (reduce_in_one_launch(g, s)) {
+        launch_reduce_vars_one(x, n, vars, result, partials, (unsigned)g, s);
+        tmark("reduce_vars", s, false);
+        return hipGetLastError();
+    }
     switch (vars.nvars) {
     case 1: launch_vars_nv<E, 1>(x, n, vars, result, partials, (unsigned)g, s); break;
     case 2: launch_vars_nv<E, 2>(x, n, vars, result, partials, (unsigned)g, s); break;
@@ -491,7 +359,10 @@ hipError_t launch_vars(const E *x, int64_t n, const RedVars &vars, E *result, vo
 
 }  // namespace
 
-size_t reduce_vars_workspace_bytes() { return sizeof(uint64_t) * RED_MAX_VARS * MAX_BLOCKS; }
+// The partials and the arrival word, in room for 4096 workgroups.
+size_t reduce_vars_workspace_bytes() { return sizeof(uint64_t) * RED_MAX_VARS * 4096; }
+size_t reduce_fast_workspace_bytes(int64_t) { return sizeof(uint32_t) * 4096; }
+static_assert(MAX_BLOCKS <= 4096 - 2, "room for the arrival word");
 
 // ---- static scratch for callers that cannot allocate -----------------------
 //
@@ -501,7 +372,8 @@ size_t reduce_vars_workspace_bytes() { return sizeof(uint64_t) * RED_MAX_VARS * 
 // never passes the array's name to a kernel (on the host it is only a
 // stand-in for the symbol), only the device address hipGetSymbolAddress gave
 // for that device.  No call needs its contents to start at zero: every
-// reduction overwrites the partials it later reads.
+// reduction overwrites the partials it later reads, and its first arrival
+// the arrival word.
 namespace {
 static __device__ __align__(256) uint64_t scratch[NOALLOC_SCRATCH_BYTES / sizeof(uint64_t)];
 constexpr int NOALLOC_MAX_DEVICES = 64;
@@ -538,8 +410,6 @@ hipError_t launch_reduce_vars(int dtype, const void *x, int64_t n, const RedVars
     default: return hipErrorInvalidValue;
     }
 }
-
-size_t reduce_fast_workspace_bytes(int64_t) { return sizeof(uint32_t) * MAX_BLOCKS; }
 
 size_t reduce_plain_workspace_bytes(int64_t n) { return sizeof(uint32_t) * (size_t)plain_blocks(n); }
 

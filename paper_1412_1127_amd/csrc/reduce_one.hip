@@ -1,0 +1,307 @@
+// Small reductions in one launch: the workgroup whose partial arrives last
+// adds all of them, in index order as the second launch of reduce.hip does,
+// so that both give the same bits.  (A file of its own, with its own copy of
+// the loops: the kernels of reduce.hip, whose code depends on what stands
+// beside it, took 16.7 us over 2^24 floats with two variables as they are and
+// 17.0 in every form that shared a file or the loops with these.)
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <random>
+#include <type_traits>
+
+#include "kernels.h"
+#include "reduce_body.h"
+
+namespace accx {
+namespace {
+
+// Whether this workgroup is the last of g to arrive; called by one thread of
+// each, after its stores of partials.  `word` counts the arrivals of one
+// call: the call's own number in the bits above ARRIVALS, the count below.  A
+// workspace may hold anything before a call, so the first to arrive puts the
+// number there; the last one leaves the word zero, which saves the next call
+// a step.  Nothing loops or waits on another workgroup.  No device-scope
+// fence is needed, which would write back the XCD's L2 (18 us over 1 GiB):
+// the partials are device-scope stores, written through to the level that
+// the XCDs share, and s_waitcnt holds the arrival back until they are there.
+constexpr uint64_t ARRIVALS = 0xfff;
+
+__device__ inline bool arrives_last(uint64_t *word, uint64_t number, unsigned g)
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((15 << 8) | (7 << 4));  // vmcnt(0)
+    asm volatile("" ::: "memory");
+    uint64_t seen = 0, count = 1;
+    if (!__hip_atomic_compare_exchange_strong(word, &seen, number + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT)) {
+        if ((seen & ~ARRIVALS) != number)
+            __hip_atomic_compare_exchange_strong(word, &seen, number, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        count = (__hip_atomic_fetch_add(word, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ARRIVALS) + 1;
+    }
+    asm volatile("" ::: "memory");
+    if (count != g) return false;
+    __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+// A workgroup's partial sum, the steps of reduce_fast; valid in thread 0.
+template <typename L> __device__ inline L fast_partial(const L *__restrict__ x, int64_t n, L *lds4)
+{
+    using V = typename Vec<L>::T;
+
+    // Aligned body of 16-byte vectors, with up to 3 leading and 3 trailing
+    // scalars (x may start at any 4-byte boundary).
+    const uintptr_t addr = (uintptr_t)x;
+    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) >> 2);
+    if (head > n) head = n;
+    const int64_t nvec = (n - head) >> 2;
+    const int64_t tail0 = head + (nvec << 2);
+    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
+
+    const int64_t stride = (int64_t)gridDim.x * RT;
+    int64_t v = (int64_t)blockIdx.x * RT + threadIdx.x;
+    V acc[RU];
+#pragma unroll
+    for (int u = 0; u < RU; ++u) acc[u] = (V)0;
+    for (; v + (RU - 1) * stride < nvec; v += RU * stride) {
+        V t[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + v + u * stride);
+#pragma unroll
+        for (int u = 0; u < RU; ++u) acc[u] += t[u];
+    }
+    for (; v < nvec; v += stride) acc[0] += __builtin_nontemporal_load(xv + v);
+    // fixed pairwise combination of the accumulators
+#pragma unroll
+    for (int w = RU / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int u = 0; u < w; ++u) acc[u] += acc[u + w];
+    L s = hsum<L>(acc[0]);
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < head) s = s + x[threadIdx.x];
+        if ((int64_t)threadIdx.x < n - tail0) s = s + x[tail0 + threadIdx.x];
+    }
+    return block_sum(s, lds4);
+}
+
+// The partials and their sum in one launch.
+template <typename L>
+__global__ __launch_bounds__(RT) void reduce_fast_one(const L *__restrict__ x, int64_t n, uint32_t *partials,
+                                                      uint64_t *word, uint64_t number, L init, L *__restrict__ result)
+{
+    __shared__ L lds4[4];
+    __shared__ bool last;
+    L s = fast_partial(x, n, lds4);
+    const unsigned g = gridDim.x;
+    if (g > 1) {
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(partials + blockIdx.x, to_bits(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = arrives_last(word, number, g);
+        }
+        __syncthreads();
+        if (!last) return;
+        s = 0;
+        for (unsigned k = threadIdx.x; k < g; k += RT)
+            s = s + from_bits<L>(__hip_atomic_load(partials + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        s = block_sum(s, lds4);
+    }
+    if (threadIdx.x == 0) result[0] = init + s;
+}
+
+// Hands a workgroup's partial of each variable, the steps of reduce_vars, to
+// put(v, operator, partial), which stores thread 0's.
+template <typename E, int NV, uint32_t SIG, typename Put>
+__device__ inline void vars_partials(const E *__restrict__ x, int64_t n, const RedVars &vars, E *lds4, Put put)
+{
+    using R = Red<E>;
+    using V = typename R::V;
+    constexpr int W = R::W;
+
+    int op[NV], sq[NV];
+    E acc[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        op[v] = SIG == SIG_RUNTIME ? vars.op[v] : (int)((SIG >> (4 * v)) & 3u);
+        sq[v] = SIG == SIG_RUNTIME ? vars.square[v] : (int)((SIG >> (4 * v + 2)) & 1u);
+        acc[v] = red_identity<E>(op[v]);
+    }
+    auto fold = [&](E t) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] = red_apply<E>(op[v], acc[v], sq[v] ? R::mul(t, t) : t);
+    };
+
+    // Aligned body of 16-byte vectors, up to W-1 leading and trailing scalars.
+    const uintptr_t addr = (uintptr_t)x;
+    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) / sizeof(E));
+    if (head > n) head = n;
+    const int64_t nvec = (n - head) / W;
+    const int64_t tail0 = head + nvec * W;
+    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
+    const int64_t stride = (int64_t)gridDim.x * RT;
+    int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x;
+    for (; i + (RU - 1) * stride < nvec; i += RU * stride) {
+        V t[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + i + u * stride);
+#pragma unroll
+        for (int u = 0; u < RU; ++u)
+#pragma unroll
+            for (int e = 0; e < W; ++e) fold(t[u][e]);
+    }
+    for (; i < nvec; i += stride) {
+        const V t = __builtin_nontemporal_load(xv + i);
+#pragma unroll
+        for (int e = 0; e < W; ++e) fold(t[e]);
+    }
+    if (blockIdx.x == 0) {
+        if ((int64_t)threadIdx.x < head) fold(x[threadIdx.x]);
+        if ((int64_t)threadIdx.x < n - tail0) fold(x[tail0 + threadIdx.x]);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) put(v, op[v], block_apply<E>(op[v], acc[v], lds4));
+}
+
+// The partials, folded and combined with the initial values in one launch.
+template <typename E, int NV, uint32_t SIG>
+__global__ __launch_bounds__(RT) void reduce_vars_one(const E *__restrict__ x, int64_t n, RedVars vars,
+                                                      uint64_t *partials, uint64_t *word, uint64_t number,
+                                                      E *__restrict__ result)
+{
+    __shared__ E lds4[4];
+    __shared__ bool last;
+    int op[NV];
+    E acc[NV];
+    const unsigned g = gridDim.x;
+    vars_partials<E, NV, SIG>(x, n, vars, lds4, [&](int v, int o, E b) {
+        op[v] = o;
+        acc[v] = b;
+        if (g > 1 && threadIdx.x == 0)
+            __hip_atomic_store(partials + (size_t)v * g + blockIdx.x, as_bits<E>(b), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    });
+    if (g > 1) {
+        if (threadIdx.x == 0) last = arrives_last(word, number, g);
+        __syncthreads();
+        if (!last) return;
+        // folds the g partials of each variable in index order
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] = red_identity<E>(op[v]);
+        for (unsigned k = threadIdx.x; k < g; k += RT)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                acc[v] = red_apply<E>(op[v], acc[v],
+                                      bits_as<E>(__hip_atomic_load(partials + (size_t)v * g + k, __ATOMIC_RELAXED,
+                                                                   __HIP_MEMORY_SCOPE_AGENT)));
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] = block_apply<E>(op[v], acc[v], lds4);
+    }
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) result[v] = red_apply<E>(op[v], bits_as<E>(vars.init[v]), acc[v]);
+    }
+}
+
+// Operator sets that are compiled: one variable (+, max, min; x or x*x), and
+// the pairs the paper's reduction loops use (SRAD's sum and sum of squares)
+// or that come as one (max and min); anything else decodes at run time.
+// Calls launch with the set as an integral constant.
+template <int NV, typename Launch> void with_operators(const RedVars &vars, Launch launch)
+{
+    uint32_t sig = 0;
+    for (int v = 0; v < NV; ++v) sig |= (uint32_t)(vars.op[v] | (vars.square[v] ? 4 : 0)) << (4 * v);
+    if constexpr (NV == 1) {
+        switch (sig) {
+        case 0x0: return launch(std::integral_constant<uint32_t, 0x0>{});
+        case 0x1: return launch(std::integral_constant<uint32_t, 0x1>{});
+        case 0x2: return launch(std::integral_constant<uint32_t, 0x2>{});
+        case 0x4: return launch(std::integral_constant<uint32_t, 0x4>{});
+        case 0x5: return launch(std::integral_constant<uint32_t, 0x5>{});
+        case 0x6: return launch(std::integral_constant<uint32_t, 0x6>{});
+        }
+    } else if constexpr (NV == 2) {
+        switch (sig) {
+        case 0x40: return launch(std::integral_constant<uint32_t, 0x40>{});  // sum, sum of squares
+        case 0x04: return launch(std::integral_constant<uint32_t, 0x04>{});  // sum of squares, sum
+        case 0x21: return launch(std::integral_constant<uint32_t, 0x21>{});  // max, min
+        case 0x12: return launch(std::integral_constant<uint32_t, 0x12>{});  // min, max
+        }
+    }
+    launch(std::integral_constant<uint32_t, SIG_RUNTIME>{});
+}
+
+// A number of one call's own, ARRIVALS and below zero, never 0: a counter from
+// a random start, mixed (splitmix64's finalizer), so that nothing that a
+// workspace can hold by chance looks like it.
+uint64_t call_number()
+{
+    static std::atomic<uint64_t> next{((uint64_t)std::random_device{}() << 32) ^ std::random_device{}()};
+    uint64_t z;
+    do {
+        z = next.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
+        z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+        z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+        z = (z ^ (z >> 31)) & ~(uint64_t)0xfff;
+    } while (z == 0);
+    return z;
+}
+
+// Whether one launch of g workgroups writes the result, or a second one folds
+// the partials.  Atomics on one word take about 20 ns
+// each, one after the other, against a launch: a float32 sum (launches back
+// to back, one against two) takes 4.4 against 5.6 us at 2 workgroups, 5.0
+// against 5.7 at 49, 5.4 against 5.7 at 64 (sum and sum of squares 5.5
+// against 6.2), but 5.9 against 5.8 at 96 and 6.7 against 5.7 at 128; words
+// in two levels were even up to 256 and 0.9 us slower at 768.  A capture is
+// replayed with one number, so that arrivals left over from replays that
+// overlapped would spoil all later ones: it keeps the two launches.
+constexpr int64_t ONE_LAUNCH = 64;
+static_assert(ONE_LAUNCH <= (int64_t)ARRIVALS, "the count in the word");
+
+}  // namespace
+
+bool reduce_in_one_launch(int64_t g, hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return g == 1 || (g <= ONE_LAUNCH && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone);
+}
+
+template <typename L>
+void launch_reduce_one(const L *x, int64_t n, L init, L *result, uint32_t *partials, unsigned g, hipStream_t s)
+{
+    hipLaunchKernelGGL(reduce_fast_one<L>, dim3(g), dim3(RT), 0, s, x, n, partials,
+                       reinterpret_cast<uint64_t *>(partials + MAX_BLOCKS), call_number(), init, result);
+}
+template void launch_reduce_one<float>(const float *, int64_t, float, float *, uint32_t *, unsigned, hipStream_t);
+template void launch_reduce_one<uint32_t>(const uint32_t *, int64_t, uint32_t, uint32_t *, uint32_t *, unsigned,
+                                          hipStream_t);
+
+template <typename E>
+void launch_reduce_vars_one(const E *x, int64_t n, const RedVars &vars, E *result, uint64_t *partials, unsigned g,
+                            hipStream_t s)
+{
+    auto run = [&](auto nv) {
+        constexpr int NV = decltype(nv)::value;
+        with_operators<NV>(vars, [&](auto sig) {
+            hipLaunchKernelGGL((reduce_vars_one<E, NV, decltype(sig)::value>), dim3(g), dim3(RT), 0, s, x, n, vars,
+                               partials, partials + RED_MAX_VARS * MAX_BLOCKS, call_number(), result);
+        });
+    };
+    switch (vars.nvars) {  // 1..RED_MAX_VARS, as the callers have checked
+    case 1: return run(std::integral_constant<int, 1>{});
+    case 2: return run(std::integral_constant<int, 2>{});
+    case 3: return run(std::integral_constant<int, 3>{});
+    default: return run(std::integral_constant<int, 4>{});
+    }
+}
+template void launch_reduce_vars_one<float>(const float *, int64_t, const RedVars &, float *, uint64_t *, unsigned,
+                                            hipStream_t);
+template void launch_reduce_vars_one<int32_t>(const int32_t *, int64_t, const RedVars &, int32_t *, uint64_t *,
+                                              unsigned, hipStream_t);
+template void launch_reduce_vars_one<double>(const double *, int64_t, const RedVars &, double *, uint64_t *, unsigned,
+                                             hipStream_t);
+template void launch_reduce_vars_one<int64_t>(const int64_t *, int64_t, const RedVars &, int64_t *, uint64_t *,
+                                              unsigned, hipStream_t);
+
+}  // namespace accx
