@@ -545,17 +545,16 @@ ACCX_API acc_status accx_server_destroy(accx_server s);
  * a hashed, 8-aligned position) as float64 dot products of the float32
  * inputs, compares them with the cheap result and marks the tile when the
  * sampled relative Frobenius error exceeds 7e-6 (0.7 x the 1e-5 bound; the
- * environment variable ACCX_PROBE_TAU overrides it); a correction pass on
- * 64 x 64 tiles then adds
- * the three missing products (hi*lo, lo*hi, mid*mid) inside the marked tiles
- * only.  One record per tile is left in the workspace (row-major tile order)
- * for inspection: */
+ * environment variable ACCX_PROBE_TAU overrides it); a correction then
+ * adds the three missing products (hi*lo, lo*hi, mid*mid) inside the marked
+ * tiles only.  One record per tile is left in the workspace (row-major tile
+ * order) for inspection: */
 typedef struct {
     int32_t rows[8], cols[8]; /* sampled rows and columns */
     double ref[64];           /* float64 dot product at (rows[u], cols[v]) in ref[8*u+v] */
     double err2, ref2;        /* sums over the samples of (C_cheap - ref)^2 and ref^2 */
     int32_t corrected;        /* 1: the tile received the correction products */
-    int32_t pad[3];
+    int32_t pad[3];           /* the library's own */
 } accx_probe_record;          /* 608 bytes */
 /* Byte offset of the records inside the workspace of accx_matmul_dev and
  * their count, for a float32 tiled call with (len, flags), flags carrying
