@@ -569,7 +569,9 @@ ACCX_API acc_status accx_gemm_probe_layout(int64_t m, int64_t n, int64_t k, uint
  * precision / limb bits of flags) on the current device, on scratch operands
  * of that shape, and records the fastest for the shape's size class (m, n
  * and k each rounded up to a power of two).  Later tiled calls with
- * ACC_TILE_AUTO in that class use it; untuned classes take a size heuristic.
+ * ACC_TILE_AUTO in that class use it; untuned classes take a size heuristic,
+ * which also runs small products in one launch without packed operands: that
+ * is faster than any tile there, so tune the large classes only.
  * Allocates and frees its scratch (charged to the budget while held).
  * best_tile_out: the ACC_TILE_* value chosen; ms_out: its kernel time (both
  * nullable).  accx_autotune(t, len, ...) is the square case.
