@@ -14,9 +14,9 @@
 //    wavefront reduces with cross-lane exchanges, the wavefronts of a
 //    workgroup combine through LDS, and each workgroup stores one partial.
 //    The partials are added in index order and then the initial value: by
-//    the workgroup whose partial arrives last if there are few of them (one
-//    launch, in which no workgroup waits for another), else by a second,
-//    one-workgroup launch.
+//    the workgroup whose partial arrives last (one launch, in which no
+//    workgroup waits for another) or by a second, one-workgroup launch: for
+//    larger sums, and under capture.
 // Both are bitwise deterministic: nothing depends on the order in which
 // workgroups finish.
 //
@@ -272,7 +272,7 @@ hipError_t launch_reduce(const L *x, int64_t n, L init, L *result, void *work, b
         const int64_t g = fast_blocks(n);
         uint32_t *partials = static_cast<uint32_t *>(work);
         tmark("reduce_fast", s, true);  // one launch or both
-        if (reduce_in_one_launch(g, s)) {
+        if (reduce_in_one_launch(g, ONE_LAUNCH_SUM, s)) {
             launch_reduce_one(x, n, init, result, partials, (unsigned)g, s);
             tmark("reduce_fast", s, false);
             return hipGetLastError();
@@ -341,7 +341,7 @@ hipError_t launch_vars(const E *x, int64_t n, const RedVars &vars, E *result, vo
     const int64_t g = fast_blocks(n * (int64_t)sizeof(E) / 4);
     uint64_t *partials = static_cast<uint64_t *>(work);
     tmark("reduce_vars", s, true);  // one launch or both
-    if (reduce_in_one_launch(g, s)) {
+    if (reduce_in_one_launch(g, ONE_LAUNCH_VARS, s)) {
         launch_reduce_vars_one(x, n, vars, result, partials, (unsigned)g, s);
         tmark("reduce_vars", s, false);
         return hipGetLastError();
@@ -359,10 +359,10 @@ hipError_t launch_vars(const E *x, int64_t n, const RedVars &vars, E *result, vo
 
 }  // namespace
 
-// The partials and the arrival word, in room for 4096 workgroups.
+// The partials and the arrival words, in room for 4096 workgroups.
 size_t reduce_vars_workspace_bytes() { return sizeof(uint64_t) * RED_MAX_VARS * 4096; }
 size_t reduce_fast_workspace_bytes(int64_t) { return sizeof(uint32_t) * 4096; }
-static_assert(MAX_BLOCKS <= 4096 - 2, "room for the arrival word");
+static_assert(MAX_BLOCKS <= 4096 - 2, "room for a sum's arrival word");
 
 // ---- static scratch for callers that cannot allocate -----------------------
 //
@@ -373,7 +373,7 @@ static_assert(MAX_BLOCKS <= 4096 - 2, "room for the arrival word");
 // stand-in for the symbol), only the device address hipGetSymbolAddress gave
 // for that device.  No call needs its contents to start at zero: every
 // reduction overwrites the partials it later reads, and its first arrival
-// the arrival word.
+// the arrival words.
 namespace {
 static __device__ __align__(256) uint64_t scratch[NOALLOC_SCRATCH_BYTES / sizeof(uint64_t)];
 constexpr int NOALLOC_MAX_DEVICES = 64;

@@ -153,8 +153,17 @@ constexpr uint32_t SIG_RUNTIME = 0xffffffffu;
 }  // namespace
 
 // One launch instead of two (reduce_one.hip), for a grid of g workgroups:
-// whether it is taken, and the launches.  `partials`: the workspace.
-bool reduce_in_one_launch(int64_t g, hipStream_t s);
+// whether it is taken, and the launches.  `partials`: the workspace.  The
+// limits: arrivals cost more the more there are, and a second launch costs
+// what it costs.  us, two launches against one, back to back: a sum (whose
+// second launch adds plain words) 5.6 / 4.4 at 2 workgroups, 5.7 / 5.0 at 49,
+// 5.7 / 5.4 at 64, then even to 256 and 5.8 / 6.9 at 768; other variables,
+// whose second launch takes longer, float32 sum and sum of squares 6.2 / 5.2
+// at 49, 6.3 / 5.4 at 256, 9.0 / 8.0 at 768 and 45.2 / 43.9 over 2^26
+// elements, float32 max 5.8 / 5.4 at 400, float64 sum 6.1 / 5.7 at 96 and
+// 7.5 / 7.3 at 768 (even, within 0.08, at 400 and 512).
+constexpr int64_t ONE_LAUNCH_SUM = 64, ONE_LAUNCH_VARS = MAX_BLOCKS;
+bool reduce_in_one_launch(int64_t g, int64_t limit, hipStream_t s);
 template <typename L>
 void launch_reduce_one(const L *x, int64_t n, L init, L *result, uint32_t *partials, unsigned g, hipStream_t s);
 template <typename E>

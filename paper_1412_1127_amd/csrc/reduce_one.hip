@@ -1,9 +1,9 @@
-// Small reductions in one launch: the workgroup whose partial arrives last
-// adds all of them, in index order as the second launch of reduce.hip does,
-// so that both give the same bits.  (A file of its own, with its own copy of
-// the loops: the kernels of reduce.hip, whose code depends on what stands
-// beside it, took 16.7 us over 2^24 floats with two variables as they are and
-// 17.0 in every form that shared a file or the loops with these.)
+// Reductions in one launch: the workgroup whose partial arrives last adds all
+// of them, in index order as the second launch of reduce.hip does, so that
+// both give the same bits.  (A file of its own, with its own copy of the
+// loops: the kernels of reduce.hip, whose code depends on what stands beside
+// it, took 16.7 us over 2^24 floats with two variables as they are and 17.0
+// in every form that shared a file or the loops with these.)
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -16,22 +16,15 @@
 namespace accx {
 namespace {
 
-// Whether this workgroup is the last of g to arrive; called by one thread of
-// each, after its stores of partials.  `word` counts the arrivals of one
-// call: the call's own number in the bits above ARRIVALS, the count below.  A
-// workspace may hold anything before a call, so the first to arrive puts the
-// number there; the last one leaves the word zero, which saves the next call
-// a step.  Nothing loops or waits on another workgroup.  No device-scope
-// fence is needed, which would write back the XCD's L2 (18 us over 1 GiB):
-// the partials are device-scope stores, written through to the level that
-// the XCDs share, and s_waitcnt holds the arrival back until they are there.
+// Whether the caller is the last of g to arrive at `word`, which counts the
+// arrivals of one call: the call's own number in the bits above ARRIVALS, the
+// count below.  A workspace may hold anything before a call, so the first to
+// arrive puts the number there; the last one leaves the word zero, which
+// saves the next call a step.  Nothing loops or waits on another workgroup.
 constexpr uint64_t ARRIVALS = 0xfff;
 
-__device__ inline bool arrives_last(uint64_t *word, uint64_t number, unsigned g)
+__device__ inline bool arrives_last_at(uint64_t *word, uint64_t number, unsigned g)
 {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((15 << 8) | (7 << 4));  // vmcnt(0)
-    asm volatile("" ::: "memory");
     uint64_t seen = 0, count = 1;
     if (!__hip_atomic_compare_exchange_strong(word, &seen, number + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT)) {
@@ -40,10 +33,39 @@ __device__ inline bool arrives_last(uint64_t *word, uint64_t number, unsigned g)
                                                  __HIP_MEMORY_SCOPE_AGENT);
         count = (__hip_atomic_fetch_add(word, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ARRIVALS) + 1;
     }
-    asm volatile("" ::: "memory");
     if (count != g) return false;
     __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
+}
+
+// Whether this workgroup is the last of g; called by one thread of each, after
+// its stores of partials.  No device-scope fence is needed, which would write
+// back the XCD's L2 (18 us over 1 GiB): the partials are device-scope stores,
+// written through to the level that the XCDs share, and s_waitcnt holds the
+// arrival back until they are there.  Atomics on one word take about 20 ns
+// each, one after the other (768 arrivals: 30 us for a sum and sum of squares
+// that takes 16), so a grid beyond ONE_WORD arrives at WORD_GROUPS words, each
+// 256 bytes from the next, and the last at each of them at a common one.
+constexpr unsigned WORD_GROUPS = 32, WORD_STRIDE = 32, ONE_WORD = 64;
+static_assert((int)ONE_WORD >= (int)WORD_GROUPS && MAX_BLOCKS <= (int)ARRIVALS &&
+                  (RED_MAX_VARS + 1) * MAX_BLOCKS + (1 + WORD_GROUPS) * WORD_STRIDE <= RED_MAX_VARS * 4096,
+              "no empty group, the count in a word, and room for the words");
+
+__device__ inline bool arrives_last(uint64_t *words, uint64_t number, unsigned g)
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((15 << 8) | (7 << 4));  // vmcnt(0)
+    asm volatile("" ::: "memory");
+    bool last = true;
+    unsigned here = g;
+    if (g > ONE_WORD) {
+        const unsigned k = blockIdx.x % WORD_GROUPS;
+        last = arrives_last_at(words + (1 + k) * WORD_STRIDE, number, (g - k + WORD_GROUPS - 1) / WORD_GROUPS);
+        here = WORD_GROUPS;
+    }
+    last = last && arrives_last_at(words, number, here);
+    asm volatile("" ::: "memory");
+    return last;
 }
 
 // A workgroup's partial sum, the steps of reduce_fast; valid in thread 0.
@@ -89,7 +111,7 @@ template <typename L> __device__ inline L fast_partial(const L *__restrict__ x, 
 // The partials and their sum in one launch.
 template <typename L>
 __global__ __launch_bounds__(RT) void reduce_fast_one(const L *__restrict__ x, int64_t n, uint32_t *partials,
-                                                      uint64_t *word, uint64_t number, L init, L *__restrict__ result)
+                                                      uint64_t *words, uint64_t number, L init, L *__restrict__ result)
 {
     __shared__ L lds4[4];
     __shared__ bool last;
@@ -98,7 +120,7 @@ __global__ __launch_bounds__(RT) void reduce_fast_one(const L *__restrict__ x, i
     if (g > 1) {
         if (threadIdx.x == 0) {
             __hip_atomic_store(partials + blockIdx.x, to_bits(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            last = arrives_last(word, number, g);
+            last = arrives_last(words, number, g);
         }
         __syncthreads();
         if (!last) return;
@@ -166,7 +188,7 @@ __device__ inline void vars_partials(const E *__restrict__ x, int64_t n, const R
 // The partials, folded and combined with the initial values in one launch.
 template <typename E, int NV, uint32_t SIG>
 __global__ __launch_bounds__(RT) void reduce_vars_one(const E *__restrict__ x, int64_t n, RedVars vars,
-                                                      uint64_t *partials, uint64_t *word, uint64_t number,
+                                                      uint64_t *partials, uint64_t *words, uint64_t number,
                                                       E *__restrict__ result)
 {
     __shared__ E lds4[4];
@@ -182,7 +204,7 @@ __global__ __launch_bounds__(RT) void reduce_vars_one(const E *__restrict__ x, i
                                __HIP_MEMORY_SCOPE_AGENT);
     });
     if (g > 1) {
-        if (threadIdx.x == 0) last = arrives_last(word, number, g);
+        if (threadIdx.x == 0) last = arrives_last(words, number, g);
         __syncthreads();
         if (!last) return;
         // folds the g partials of each variable in index order
@@ -247,24 +269,14 @@ uint64_t call_number()
     return z;
 }
 
-// Whether one launch of g workgroups writes the result, or a second one folds
-// the partials.  Atomics on one word take about 20 ns
-// each, one after the other, against a launch: a float32 sum (launches back
-// to back, one against two) takes 4.4 against 5.6 us at 2 workgroups, 5.0
-// against 5.7 at 49, 5.4 against 5.7 at 64 (sum and sum of squares 5.5
-// against 6.2), but 5.9 against 5.8 at 96 and 6.7 against 5.7 at 128; words
-// in two levels were even up to 256 and 0.9 us slower at 768.  A capture is
-// replayed with one number, so that arrivals left over from replays that
-// overlapped would spoil all later ones: it keeps the two launches.
-constexpr int64_t ONE_LAUNCH = 64;
-static_assert(ONE_LAUNCH <= (int64_t)ARRIVALS, "the count in the word");
-
 }  // namespace
 
-bool reduce_in_one_launch(int64_t g, hipStream_t s)
+bool reduce_in_one_launch(int64_t g, int64_t limit, hipStream_t s)
 {
+    // A capture is replayed with one number, so that arrivals left over from
+    // replays that overlapped would spoil all later ones: two launches.
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return g == 1 || (g <= ONE_LAUNCH && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone);
+    return g == 1 || (g <= limit && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone);
 }
 
 template <typename L>

@@ -2,7 +2,7 @@
 against the two-launch form that a capture records: both add the same
 partials in the same order, so they agree bit for bit, whatever the workspace
 held before.  The sizes give one workgroup, two, three, the largest number
-that one launch takes (for either element type) and one more, and a full
+that arrives at one word (for either element type) and one more, and a full
 grid, with ragged ends."""
 import numpy as np
 import pytest
