@@ -362,7 +362,6 @@ hipError_t launch_vars(const E *x, int64_t n, const RedVars &vars, E *result, vo
 // The partials and the arrival words, in room for 4096 workgroups.
 size_t reduce_vars_workspace_bytes() { return sizeof(uint64_t) * RED_MAX_VARS * 4096; }
 size_t reduce_fast_workspace_bytes(int64_t) { return sizeof(uint32_t) * 4096; }
-static_assert(MAX_BLOCKS <= 4096 - 2, "room for a sum's arrival word");
 
 // ---- static scratch for callers that cannot allocate -----------------------
 //

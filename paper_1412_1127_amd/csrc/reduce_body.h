@@ -155,14 +155,14 @@ constexpr uint32_t SIG_RUNTIME = 0xffffffffu;
 // One launch instead of two (reduce_one.hip), for a grid of g workgroups:
 // whether it is taken, and the launches.  `partials`: the workspace.  The
 // limits: arrivals cost more the more there are, and a second launch costs
-// what it costs.  us, two launches against one, back to back: a sum (whose
-// second launch adds plain words) 5.6 / 4.4 at 2 workgroups, 5.7 / 5.0 at 49,
-// 5.7 / 5.4 at 64, then even to 256 and 5.8 / 6.9 at 768; other variables,
-// whose second launch takes longer, float32 sum and sum of squares 6.2 / 5.2
-// at 49, 6.3 / 5.4 at 256, 9.0 / 8.0 at 768 and 45.2 / 43.9 over 2^26
-// elements, float32 max 5.8 / 5.4 at 400, float64 sum 6.1 / 5.7 at 96 and
-// 7.5 / 7.3 at 768 (even, within 0.08, at 400 and 512).
-constexpr int64_t ONE_LAUNCH_SUM = 64, ONE_LAUNCH_VARS = MAX_BLOCKS;
+// what it costs.  us a call, two launches / one: a float32 or int32 sum
+// (whose second launch adds plain words) 8.2 / 5.6 at 13 workgroups, 8.3 /
+// 5.7 at 86 to 184, 8.3 / 8.1 at 245, 8.4 / 7.8 at 367 to 489, but 9.7 / 10.3
+// at 733 and 11.6 / 12.5 at 768; other variables, whose second launch takes
+// longer, at every size: float64 sum 8.9 / 5.9 at 98, 9.0 / 7.1 at 391, 8.9 /
+// 8.5 at 489, float32 sum and sum of squares 9.2 / 6.2 at 98, 11.2 / 10.4 at
+// 733, 16.6 / 15.7 over 2^24 elements, max and min 9.3 / 8.4 at 367.
+constexpr int64_t ONE_LAUNCH_SUM = 512, ONE_LAUNCH_VARS = MAX_BLOCKS;
 bool reduce_in_one_launch(int64_t g, int64_t limit, hipStream_t s);
 template <typename L>
 void launch_reduce_one(const L *x, int64_t n, L init, L *result, uint32_t *partials, unsigned g, hipStream_t s);

@@ -48,7 +48,8 @@ __device__ inline bool arrives_last_at(uint64_t *word, uint64_t number, unsigned
 // 256 bytes from the next, and the last at each of them at a common one.
 constexpr unsigned WORD_GROUPS = 32, WORD_STRIDE = 32, ONE_WORD = 64;
 static_assert((int)ONE_WORD >= (int)WORD_GROUPS && MAX_BLOCKS <= (int)ARRIVALS &&
-                  (RED_MAX_VARS + 1) * MAX_BLOCKS + (1 + WORD_GROUPS) * WORD_STRIDE <= RED_MAX_VARS * 4096,
+                  8 * (1 + WORD_GROUPS) * WORD_STRIDE <= 4 * (4096 - MAX_BLOCKS) &&
+                  RED_MAX_VARS * MAX_BLOCKS + (1 + WORD_GROUPS) * WORD_STRIDE <= RED_MAX_VARS * 4096,
               "no empty group, the count in a word, and room for the words");
 
 __device__ inline bool arrives_last(uint64_t *words, uint64_t number, unsigned g)

@@ -2,8 +2,9 @@
 against the two-launch form that a capture records: both add the same
 partials in the same order, so they agree bit for bit, whatever the workspace
 held before.  The sizes give one workgroup, two, three, the largest number
-that arrives at one word (for either element type) and one more, and a full
-grid, with ragged ends."""
+that arrives at one word (for either element type) and one more, the largest
+that takes one launch for a plain sum and one more, and a full grid, with
+ragged ends."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,8 @@ from _util import SEED
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 8192, 8197, 16389, 100003, 32 * 8192 + 1, 64 * 8192 + 3, 64 * 8192 + 4, 768 * 8192 + 8195]
+SIZES = [1, 8192, 8197, 16389, 100003, 32 * 8192 + 1, 64 * 8192 + 3, 64 * 8192 + 4, 512 * 8192, 512 * 8192 + 4,
+         768 * 8192 + 8195]
 
 
 @pytest.fixture(scope="module")
