@@ -654,6 +654,20 @@ hipError_t cheap_pass(const char *pa, const char *pbt, float *c, const GemmShape
     return accx::launch_gemm_bf16x3(pa, pbt, c, sh, 3, false, tile, s, nullptr, sk);
 }
 
+// Whether the kernels that read A and B themselves (the direct paths, the
+// correction of listed tiles) may run: leading dimensions within their 32-bit
+// offsets, and no byte of C's span in A's or B's, since they read operands
+// after other workgroups have written parts of C.  The packed path has read
+// both operands before its first store to C.
+bool reads_operands(const void *a, const void *b, const void *c, const GemmShape &sh)
+{
+    if (sh.lda > accx::DIRECT_MAX_LD || sh.ldb > accx::DIRECT_MAX_LD) return false;
+    const uintptr_t c0 = (uintptr_t)c, c1 = c0 + (uintptr_t)span_elems(sh.m, sh.n, sh.ldc) * 4;
+    const uintptr_t a0 = (uintptr_t)a, a1 = a0 + (uintptr_t)span_elems(sh.m, sh.k, sh.lda) * 4;
+    const uintptr_t b0 = (uintptr_t)b, b1 = b0 + (uintptr_t)span_elems(sh.k, sh.n, sh.ldb) * 4;
+    return (c1 <= a0 || a1 <= c0) && (c1 <= b0 || b1 <= c0);
+}
+
 acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmShape &sh, uint32_t flags, char *work,
                          size_t work_bytes, hipStream_t s, const CoReduce *red = nullptr)
 {
@@ -668,7 +682,8 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     }
     const DirectChoice dc = direct_choice(sh, flags);
     const uint32_t prec = flags & ACC_PREC_MASK;
-    if (dc.tile && sh.lda <= accx::DIRECT_MAX_LD && sh.ldb <= accx::DIRECT_MAX_LD) {
+    const bool reads = reads_operands(a, b, c, sh);
+    if (dc.tile && reads) {
         accx::SplitK dk;
         // the partial sums take the place of the packed operands
         if (dc.parts > 1 && accx::split_k_bytes(dc.tile, sh.m, sh.n, dc.parts) <= packed_pair(sh, 2, 3)) {
@@ -694,7 +709,7 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
         // default that each launch would resolve on its own.
         ptile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
         if (!ptile) ptile = dc.tile ? dc.tile : accx::default_tile(sh.m, sh.n);
-        listed = ptile != accx::GEMM_TILE_64 && sh.k > 0 && sh.lda <= accx::DIRECT_MAX_LD && sh.ldb <= accx::DIRECT_MAX_LD;
+        listed = ptile != accx::GEMM_TILE_64 && sh.k > 0 && reads;
     }
     hipError_t e = accx::launch_pack_bf16x3_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s,
                                                  listed ? &rec->count : nullptr);
@@ -702,8 +717,8 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     if (prec == ACC_PREC_AUTO) {
         // cheap pass, float64 probe per tile, then the three missing products
         // on the tiles the probe marked.
-        // Rows too long for the direct path: its tile (the records' layout
-        // does not depend on leading dimensions), unsplit.
+        // Operands the direct path does not take: its tile (the records'
+        // layout depends on the shape alone), unsplit.
         if (dc.tile) sk = accx::SplitK();
         e = cheap_pass(pa, pbt, c, sh, ptile, sk, red, s);
         accx::RedFinal fin;
@@ -742,7 +757,7 @@ acc_status run_tiled_i32(const int32_t *a, const int32_t *b, int32_t *c, const G
                          char *work, size_t work_bytes, hipStream_t s)
 {
     const DirectChoice dc = direct_choice_i32(sh, flags);
-    if (dc.tile && sh.lda <= accx::DIRECT_MAX_LD && sh.ldb <= accx::DIRECT_MAX_LD) {
+    if (dc.tile && reads_operands(a, b, c, sh)) {
         accx::SplitK dk;
         // the partial sums take the place of the packed operands
         if (dc.parts > 1 && accx::split_k_bytes(dc.tile, sh.m, sh.n, dc.parts) <= packed_pair(sh, 1, 4)) {
