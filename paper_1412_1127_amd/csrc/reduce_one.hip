@@ -275,9 +275,19 @@ uint64_t call_number()
 bool reduce_in_one_launch(int64_t g, int64_t limit, hipStream_t s)
 {
     // A capture is replayed with one number, so that arrivals left over from
-    // replays that overlapped would spoil all later ones: two launches.
+    // replays that overlapped would spoil all later ones: two launches.  The
+    // null stream cannot be captured, and is not asked: while a blocking
+    // stream is under capture the query itself fails there, and its error
+    // would be taken for the launch's.
+    if (g == 1) return true;
+    if (g > limit) return false;
+    if (s == nullptr) return true;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return g == 1 || (g <= limit && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone);
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusNone;
 }
 
 template <typename L>
