@@ -7,7 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
-#include <random>
+#include <chrono>
 #include <type_traits>
 
 #include "kernels.h"
@@ -254,12 +254,16 @@ template <int NV, typename Launch> void with_operators(const RedVars &vars, Laun
     launch(std::integral_constant<uint32_t, SIG_RUNTIME>{});
 }
 
-// A number of one call's own, ARRIVALS and below zero, never 0: a counter from
-// a random start, mixed (splitmix64's finalizer), so that nothing that a
-// workspace can hold by chance looks like it.
-uint64_t call_number()
+// A number of one call's own, ARRIVALS and below zero, never 0: a counter,
+// mixed (splitmix64's finalizer), so that nothing that a workspace can hold by
+// chance looks like it.  It starts from the clock and from where this process
+// was loaded, so that numbers an earlier process left in memory differ too;
+// std::random_device may throw, which no C entry may.
+uint64_t call_number() noexcept
 {
-    static std::atomic<uint64_t> next{((uint64_t)std::random_device{}() << 32) ^ std::random_device{}()};
+    static std::atomic<uint64_t> next{
+        (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull +
+        (uint64_t)(uintptr_t)&next};
     uint64_t z;
     do {
         z = next.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
