@@ -541,13 +541,21 @@ int resolve_tile(int t, const GemmShape &sh, uint32_t flags, int limbs)
 // 0: the packed path.  The direct tile splits and loads its operands itself,
 // so it pays while its tiles come in one round of workgroups (one per CU), or
 // little more: measured, us per call, packed against direct, AUTO: LEN = 256
-// 18.4 / 9.2, 1000 40 / 19, 1531 73 / 44, 2048 98 / 68, 3072 (2.3 rounds of
-// 128 x 128) 294 / 252, 3500 (3.1 rounds) 390 / 402; six products: 256 10.8 /
-// 7.5, 1000 31 / 21, 2048 109 / 98, 2200 (1.3 rounds) 176 / 181.  Beyond one
+// 17.8 / 9.1, 1000 39 / 18, 1531 71 / 42, 2048 96 / 64, 3072 (2.3 rounds of
+// 128 x 128) 280 / 239, 3500 (3.1 rounds) 358 / 357; six products: 256 10.8 /
+// 7.5, 1000 29 / 19, 2048 105 / 89, 2200 (1.3 rounds) 165 / 165.  Beyond one
 // round the packed path's larger tiles win: 4096 x 4096 x 512 75 / 87.
+// Without the probe (CHEAP3) the packed path is two launches, and wins between
+// one and two rounds on long loops (2060 93 / 98, 2700 139 / 144, but 3072 241
+// / 219 and 9000 x 500 x 1000 66 / 55) and beyond one round on short ones
+// (3000 x 3000 x 16 20.0 / 22.1, 2040 x 2300 x 200 22.4 / 23.3).
 // Among 64 x 64 tiles, 128 x 128 tiles and K parts the estimate below picks:
-// a base (launch, first loads, probe, stores) and a time per k and round, both
-// fitted to those runs, and for parts the ticket launch and the partial sums.
+// a base (launch, first loads, probe, stores), the same again, but for the
+// launch, for each further round, and a time per k and round, all fitted to
+// runs like those, and for parts the ticket launch and the partial sums.  (K =
+// 32, us, 64 x 64 / 128 x 128 tiles: AUTO 2048 x 2048 24.7 / 11.1, 3000 x 3000
+// 51 / 27, packed 39; CHEAP3 1500 x 1500 13.0 / 8.1; six products 2048 x 2048
+// 14.8 / 9.7.)
 struct DirectChoice {
     int tile = 0, parts = 1;
 };
@@ -559,20 +567,23 @@ DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
     const uint32_t prec = flags & ACC_PREC_MASK;
     const uint32_t f = prec == ACC_PREC_AUTO ? (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3 : flags;
     if (resolve_tile(ACC_FLOAT32, sh, f, 0)) return best;
-    const bool three = prec == ACC_PREC_AUTO || prec == ACC_PREC_CHEAP3;
+    const bool probed = prec == ACC_PREC_AUTO, three = probed || prec == ACC_PREC_CHEAP3;
     const int64_t cus = accx::device_cu_count();
     const int64_t t128 = ((sh.m + 127) / 128) * ((sh.n + 127) / 128), t64 = ((sh.m + 63) / 64) * ((sh.n + 63) / 64);
     if (2 * t128 > (three ? 5 : 2) * cus) return best;
+    if (prec == ACC_PREC_CHEAP3 && t128 > cus && (sh.k < 256 || (sh.k > 1024 && t128 <= 2 * cus))) return best;
     double best_us = 1e300;
     for (int tile : {accx::GEMM_TILE_64, accx::GEMM_TILE_128}) {
         const bool small = tile == accx::GEMM_TILE_64;
         const int64_t tiles = small ? t64 : t128;
         const double base = small ? (three ? 7.0 : 5.5) : (three ? 9.5 : 8.5);
+        const double more = small ? (probed ? 5.0 : three ? 3.3 : 2.5) : (probed ? 6.9 : three ? 5.2 : 4.9);
         const double per_k = small ? (three ? 0.0127 : 0.0165) : (three ? 0.0296 : 0.045);
         for (int parts = 1; parts <= 8; ++parts) {
             if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256)) break;
             const double rounds = (double)((tiles * parts + cus - 1) / cus);
-            const double us = base + rounds * per_k * (double)sh.k / parts + (parts > 1 ? 5.0 + parts : 0.0);
+            const double us = base + (rounds - 1.0) * more + rounds * per_k * (double)sh.k / parts +
+                              (parts > 1 ? 5.0 + parts : 0.0);
             if (us < best_us) {
                 best_us = us;
                 best.tile = tile;

@@ -1,0 +1,81 @@
+"""Which kernels a float32 product of open tile runs on, on both sides of each
+line: short loops over several rounds of tiles on the larger tile, three
+products without a probe on the packed path where it is the faster one; and
+the results there, against the oracle or float64.  (The lines depend on the number of
+compute units; the sizes are those of 256.)"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from _util import FP32_REL_FRO_TOL, SEED, rel_fro
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ax():
+    import torch
+
+    import paper_1412_1127_amd as ax
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("sizes for 256 compute units")
+    ax.acc_init(0, 0)
+    yield ax
+    ax.acc_shutdown()
+
+
+def _flags(ax, prec):
+    return ax.ACC_KERNEL_TILED | {"auto": ax.ACC_PREC_AUTO, "full6": ax.ACC_PREC_FULL6, "five": ax.ACC_PREC_FIVE,
+                                  "cheap3": ax.ACC_PREC_CHEAP3}[prec]
+
+
+# short loops: 64 x 64 tiles in several rounds pay a round trip to memory (and
+# a probe) per round; the probe records show the tile that ran
+@pytest.mark.parametrize("m,n,k,edge", [(1000, 1000, 16, 64), (1030, 1030, 16, 128), (2048, 2048, 32, 128),
+                                        (3000, 3000, 32, 128), (2200, 2200, 130, 128), (2500, 2500, 64, 128),
+                                        (9000, 500, 33, 128), (1000, 1000, 1000, 64)])
+def test_tile_of_short_loops(ax, m, n, k, edge):
+    import torch
+    fl = _flags(ax, "auto")
+    off, cnt = ax.accx_gemm_probe_layout(m, n, k, fl)
+    assert cnt == -(-m // edge) * -(-n // edge)
+    a, b = synth.uniform_pm1_f32((m, k), SEED, 9500), synth.uniform_pm1_f32((k, n), SEED, 9501)
+    da, db, dc = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), torch.full((m, n), float("nan"), device="cuda")
+    ws = ax.accx_gemm_workspace_size(ax.ACC_FLOAT32, m, n, k, fl)
+    work = torch.full((ws,), 0xFF, dtype=torch.uint8, device="cuda")
+    print("short loop m=%d n=%d k=%d" % (m, n, k), flush=True)
+    ax.accx_gemm_dev(ax.ACC_FLOAT32, m, n, k, da, k, db, n, dc, n, fl, work, ws)
+    torch.cuda.synchronize()
+    assert rel_fro(dc.cpu().numpy(), oracle.gemm(a, b)) <= FP32_REL_FRO_TOL
+    recs = ax.probe_records(work[off:off + cnt * 608].cpu().numpy().tobytes(), cnt)
+    # every record was written, its samples inside its tile
+    nt = -(-n // edge)
+    for q, r in enumerate(recs):
+        assert q // nt * edge <= min(r.rows) and max(r.rows) < min(m, (q // nt + 1) * edge)
+        assert q % nt * edge <= min(r.cols) and max(r.cols) < min(n, (q % nt + 1) * edge)
+
+
+@pytest.mark.parametrize("prec,m,n,k,direct", [
+    ("cheap3", 2048, 2048, 64, True), ("cheap3", 2060, 2060, 64, False), ("cheap3", 2060, 2060, 600, True),
+    ("cheap3", 2060, 2060, 1100, False), ("cheap3", 2950, 2950, 1100, True), ("cheap3", 3000, 3000, 64, False),
+    ("five", 2048, 2048, 128, True), ("five", 2060, 2060, 128, False), ("full6", 1030, 1030, 800, True), ("full6", 2048, 2048, 128, True),
+    ("full6", 2060, 2060, 128, False)])
+def test_route(ax, prec, m, n, k, direct):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    da = torch.rand((m, k), generator=g, device="cuda") * 2 - 1
+    db = torch.rand((k, n), generator=g, device="cuda") * 2 - 1
+    dc = torch.full((m, n), float("nan"), device="cuda")
+    print("route %s m=%d n=%d k=%d" % (prec, m, n, k), flush=True)
+    ax.accx_timing_enable(True)
+    ax.accx_timing_read(reset=True)
+    ax.accx_gemm_dev(ax.ACC_FLOAT32, m, n, k, da, k, db, n, dc, n, _flags(ax, prec))
+    torch.cuda.synchronize()
+    names = set(ax.accx_timing_read(reset=True))
+    ax.accx_timing_enable(False)
+    assert names == ({"gemm_direct"} if direct else {"pack_bf16x3", "gemm_bf16x3"}), names
+    ref = da.double() @ db.double()
+    err = float((dc.double() - ref).norm() / ref.norm())
+    assert err <= FP32_REL_FRO_TOL, err
