@@ -552,7 +552,9 @@ int resolve_tile(int t, const GemmShape &sh, uint32_t flags, int limbs)
 // Among 64 x 64 tiles, 128 x 128 tiles and K parts the estimate below picks:
 // a base (launch, first loads, probe, stores), the same again, but for the
 // launch, for each further round, and a time per k and round, all fitted to
-// runs like those, and for parts the ticket launch and the partial sums.  (K =
+// runs like those, and for parts, as many as the workspace holds, the ticket
+// launch and the partial sums (six products, LEN = 1030, 128 x 128 tiles: one
+// part 38.6, two 31.4, packed 36.6; three do not fit).  (K =
 // 32, us, 64 x 64 / 128 x 128 tiles: AUTO 2048 x 2048 24.7 / 11.1, 3000 x 3000
 // 51 / 27, packed 39; CHEAP3 1500 x 1500 13.0 / 8.1; six products 2048 x 2048
 // 14.8 / 9.7.)
@@ -580,7 +582,10 @@ DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
         const double more = small ? (probed ? 5.0 : three ? 3.3 : 2.5) : (probed ? 6.9 : three ? 5.2 : 4.9);
         const double per_k = small ? (three ? 0.0127 : 0.0165) : (three ? 0.0296 : 0.045);
         for (int parts = 1; parts <= 8; ++parts) {
-            if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256)) break;
+            // (the partial sums take the place of the packed operands)
+            if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256 ||
+                              accx::split_k_bytes(tile, sh.m, sh.n, parts) > packed_pair(sh, 2, 3)))
+                break;
             const double rounds = (double)((tiles * parts + cus - 1) / cus);
             const double us = base + (rounds - 1.0) * more + rounds * per_k * (double)sh.k / parts +
                               (parts > 1 ? 5.0 + parts : 0.0);
@@ -616,7 +621,9 @@ DirectChoice direct_choice_i32(const GemmShape &sh, uint32_t flags)
         const int64_t tiles = ((sh.m + edge - 1) / edge) * ((sh.n + edge - 1) / edge);
         if (tiles > cus) continue;
         for (int parts = 1; parts <= 8; ++parts) {
-            if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256)) break;
+            if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256 ||
+                              accx::split_k_bytes(tile, sh.m, sh.n, parts) > packed_pair(sh, 1, 4)))
+                break;
             const double us = (edge == 64 ? 4.8 : 5.5) + (edge == 64 ? 0.0115 : 0.0225) * (double)sh.k / parts +
                               (parts > 1 ? 3.0 + 0.6 * parts : 0.0);
             if (us < best_us) {
@@ -696,11 +703,8 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     const bool reads = reads_operands(a, b, c, sh);
     if (dc.tile && reads) {
         accx::SplitK dk;
-        // the partial sums take the place of the packed operands
-        if (dc.parts > 1 && accx::split_k_bytes(dc.tile, sh.m, sh.n, dc.parts) <= packed_pair(sh, 2, 3)) {
-            dk.parts = dc.parts;
-            dk.work = work;
-        }
+        dk.parts = dc.parts;
+        dk.work = work;
         auto *rec = prec == ACC_PREC_AUTO ? reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh)) : nullptr;
         return check_launch(accx::launch_gemm_direct(a, b, c, sh,
                                                      prec == ACC_PREC_FULL6 ? 6 : prec == ACC_PREC_FIVE ? 5 : 3, dc.tile,
@@ -770,11 +774,8 @@ acc_status run_tiled_i32(const int32_t *a, const int32_t *b, int32_t *c, const G
     const DirectChoice dc = direct_choice_i32(sh, flags);
     if (dc.tile && reads_operands(a, b, c, sh)) {
         accx::SplitK dk;
-        // the partial sums take the place of the packed operands
-        if (dc.parts > 1 && accx::split_k_bytes(dc.tile, sh.m, sh.n, dc.parts) <= packed_pair(sh, 1, 4)) {
-            dk.parts = dc.parts;
-            dk.work = work;
-        }
+        dk.parts = dc.parts;
+        dk.work = work;
         return check_launch(accx::launch_gemm_i8_direct(a, b, c, sh, dc.tile, s, dk), "gemm (int8, direct) launch");
     }
     const accx::SplitK sk = split_for(ACC_INT32, sh, flags, work, work_bytes);

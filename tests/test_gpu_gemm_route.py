@@ -79,3 +79,38 @@ def test_route(ax, prec, m, n, k, direct):
     ref = da.double() @ db.double()
     err = float((dc.double() - ref).norm() / ref.norm())
     assert err <= FP32_REL_FRO_TOL, err
+
+
+@pytest.mark.parametrize("dtype", ["f32", "i32"])
+@pytest.mark.parametrize("m,n,k,parts", [(1030, 1030, 1030, True), (1100, 1100, 1100, True), (1030, 1030, 500, False),
+                                         (300, 260, 1200, True)])
+def test_k_parts_that_fit_the_workspace(ax, dtype, m, n, k, parts):
+    # an estimate that asks for more K parts than the workspace holds would
+    # run unsplit; parts leave their sums in the workspace, and nothing else
+    # on this path writes there (six products have no probe records)
+    import torch
+    if dtype == "i32":
+        if m > 1000:
+            pytest.skip("int32 products of this size run packed")
+        a, b = synth.int_uniform_i32((m, k), -16, 16, SEED, 9510), synth.int_uniform_i32((k, n), -16, 16, SEED, 9511)
+        t, fl = ax.ACC_INT32, ax.ACC_KERNEL_TILED
+    else:
+        a, b = synth.uniform_pm1_f32((m, k), SEED, 9510), synth.uniform_pm1_f32((k, n), SEED, 9511)
+        t, fl = ax.ACC_FLOAT32, _flags(ax, "full6")
+    da, db = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+    dc = torch.zeros((m, n), dtype=da.dtype, device="cuda")
+    ws = ax.accx_gemm_workspace_size(t, m, n, k, fl)
+    work = torch.full((ws + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    print("parts %s m=%d n=%d k=%d" % (dtype, m, n, k), flush=True)
+    ax.accx_timing_enable(True)
+    ax.accx_timing_read(reset=True)
+    ax.accx_gemm_dev(t, m, n, k, da, k, db, n, dc, n, fl, work, ws)
+    torch.cuda.synchronize()
+    names = set(ax.accx_timing_read(reset=True))
+    ax.accx_timing_enable(False)
+    assert names == {"gemm_i8_direct" if dtype == "i32" else "gemm_direct"}, names
+    assert bool((work[:ws] != 0xA5).any().item()) == parts
+    assert bool((work[ws:] == 0xA5).all().item())
+    ref = oracle.gemm(a, b)
+    c = dc.cpu().numpy()
+    assert np.array_equal(c, ref) if dtype == "i32" else rel_fro(c, ref) <= FP32_REL_FRO_TOL
