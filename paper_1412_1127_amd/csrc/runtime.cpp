@@ -603,19 +603,22 @@ DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
 // (launch_gemm_i8_direct).  The values are not known here, so the direct path
 // is taken where it is the faster one on one-digit data, the packed path's
 // best case: us per call, packed against direct, values in [-16, 16] and (full
-// range): LEN = 256 15.3 / 7.1 (23 / 8.5), 512 16.1 / 9.9 (34 / 12.4), 1000
-// 18.2 / 16.6 (61 / 23), 1300 23.8 / 28 (88 / 41), 128 x 128 x 4096 20.6 /
-// 18.2 (133 / 23).  Both estimates are fitted to those runs.
+// range): LEN = 256 12.4 / 7.2 (22 / 8.2), 512 13.3 / 9.9 (31 / 11.6), 1000
+// 17.1 / 16.4 (52 / 21), 1300 23.4 / 37 (72 / 49), 128 x 128 x 4096 18.8 / 15.2
+// (127 / 17.1), 2048 x 2048 x 256 15.5 / 13.2 (31 / 17.5), 2048 x 2048 x 512
+// 17.6 / 18.3 (45 / 27), 1664 x 2096 x 652 19.8 / 23.5 (50 / 33).  Both
+// estimates are fitted to runs like those: the direct one's time per k grows
+// with the share of CUs at work, whose loads meet in the L2.
 DirectChoice direct_choice_i32(const GemmShape &sh, uint32_t flags)
 {
     DirectChoice best;
     if (is_plain(flags) || flag_limbs(flags) || sh.m == 0 || sh.n == 0 || resolve_tile(ACC_INT32, sh, flags, 1))
         return best;
     const int64_t cus = accx::device_cu_count();
-    const double mnk = (double)sh.m * (double)sh.n * (double)sh.k;
+    const double k = (double)sh.k, mnk = (double)sh.m * (double)sh.n * k;
     const bool splits = split_plan(ACC_INT32, sh, flags).parts > 1;  // the packed path: a ticket launch more
-    double best_us =
-        0.95 * ((splits ? 18.0 : 14.0) + 5.0 * (double)(sh.m + sh.n) * (double)sh.k / 3.5e6 + 2.0 * mnk / 1.2e9);
+    double best_us = 5.0 * (double)(sh.m + sh.n) * k / 3.5e6 + 2.0 * mnk / 1.2e9;
+    best_us = splits ? 0.95 * (16.2 + 0.0006 * k + best_us) : 12.2 + best_us;
     for (int tile : {accx::GEMM_TILE_64, accx::GEMM_TILE_128}) {
         const int64_t edge = tile == accx::GEMM_TILE_64 ? 64 : 128;
         const int64_t tiles = ((sh.m + edge - 1) / edge) * ((sh.n + edge - 1) / edge);
@@ -624,8 +627,10 @@ DirectChoice direct_choice_i32(const GemmShape &sh, uint32_t flags)
             if (parts > 1 && (tiles * parts > cus || sh.k / parts < 256 ||
                               accx::split_k_bytes(tile, sh.m, sh.n, parts) > packed_pair(sh, 1, 4)))
                 break;
-            const double us = (edge == 64 ? 4.8 : 5.5) + (edge == 64 ? 0.0115 : 0.0225) * (double)sh.k / parts +
-                              (parts > 1 ? 3.0 + 0.6 * parts : 0.0);
+            const double busy = (double)(tiles * parts) / (double)cus;
+            const double us = (edge == 64 ? 4.6 + (0.0097 + 0.0021 * busy) * k / parts
+                                          : 5.2 + 2.4 * busy + 0.023 * k / parts) +
+                              (parts > 1 ? 2.0 + 0.45 * parts : 0.0);
             if (us < best_us) {
                 best_us = us;
                 best.tile = tile;

@@ -1,7 +1,7 @@
-"""Which kernels a float32 product of open tile runs on, on both sides of each
+"""Which kernels a product of open tile runs on, on both sides of each
 line: short loops over several rounds of tiles on the larger tile, three
-products without a probe on the packed path where it is the faster one; and
-the results there, against the oracle or float64.  (The lines depend on the number of
+products without a probe, and int32, on the packed path where it is the faster
+one; and the results there, against the oracle or float64.  (The lines depend on the number of
 compute units; the sizes are those of 256.)"""
 import numpy as np
 import pytest
@@ -79,6 +79,27 @@ def test_route(ax, prec, m, n, k, direct):
     ref = da.double() @ db.double()
     err = float((dc.double() - ref).norm() / ref.norm())
     assert err <= FP32_REL_FRO_TOL, err
+
+
+@pytest.mark.parametrize("m,n,k,direct", [
+    (1000, 1000, 1000, True), (1300, 1300, 1300, False), (2048, 2048, 256, True), (2048, 2048, 512, False),
+    (1664, 2096, 652, False), (3372, 607, 469, False), (3372, 608, 200, True), (64, 64, 4096, True),
+    (130, 75, 4200, True), (128, 128, 8192, True), (300, 1000, 4000, True)])
+def test_route_i32(ax, m, n, k, direct):
+    # the direct path where it is the faster one on one-digit values
+    import torch
+    a, b = synth.int_uniform_i32((m, k), -16, 16, SEED, 9520), synth.int_uniform_i32((k, n), -16, 16, SEED, 9521)
+    da, db = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+    dc = torch.full((m, n), 77, dtype=torch.int32, device="cuda")
+    print("route i32 m=%d n=%d k=%d" % (m, n, k), flush=True)
+    ax.accx_timing_enable(True)
+    ax.accx_timing_read(reset=True)
+    ax.accx_gemm_dev(ax.ACC_INT32, m, n, k, da, k, db, n, dc, n, ax.ACC_KERNEL_TILED)
+    torch.cuda.synchronize()
+    names = set(ax.accx_timing_read(reset=True))
+    ax.accx_timing_enable(False)
+    assert ("gemm_i8_direct" in names) == direct and ("pack_i8" in names) != direct, names
+    assert np.array_equal(dc.cpu().numpy(), oracle.gemm(a, b))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "i32"])
