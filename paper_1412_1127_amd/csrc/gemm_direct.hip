@@ -164,22 +164,11 @@ struct CorrPlan {
     int max_parts;
 };
 
-__global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan c, RedFinal fin)
+__global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan c)
 {
     constexpr int BM = 128, KS = 16, NBLK = 4, WORDS = BM * BM;
     __shared__ __attribute__((aligned(1024))) char lds[direct_lds_bytes<BM, BM, KS, 3, PL_CORR3>()];
     __shared__ int last_part;
-    if (fin.result && blockIdx.x == 0) {
-        float *w4 = reinterpret_cast<float *>(lds);
-        float v = 0.0f;
-        for (int k = threadIdx.x; k < fin.parts; k += 256) v += __uint_as_float(fin.part[k]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if ((threadIdx.x & 63) == 0) w4[threadIdx.x >> 6] = v;
-        __syncthreads();
-        if (threadIdx.x == 0) *fin.result = fin.init + ((w4[0] + w4[1]) + (w4[2] + w4[3]));
-        __syncthreads();
-    }
     const int count = __builtin_amdgcn_readfirstlane(c.rec[0].count);
     if (count == 0) return;
     const int subs = c.subs_m * c.subs_n;
@@ -249,7 +238,7 @@ hipError_t launch(const DirectArgs &g, const DirectPlan &pl, hipStream_t s)
 }  // namespace
 
 hipError_t launch_correction(const float *a, const float *b, float *c, const GemmShape &sh, int tile, ProbeRecord *rec,
-                             void *work, size_t work_bytes, int max_parts, hipStream_t s, const RedFinal &fin)
+                             void *work, size_t work_bytes, int max_parts, hipStream_t s)
 {
     int bm, bn;
     tile_dims(tile, sh.m, sh.n, bm, bn);
@@ -258,7 +247,7 @@ hipError_t launch_correction(const float *a, const float *b, float *c, const Gem
     const CorrPlan p{rec, (int)((sh.n + bn - 1) / bn), bm / 128, bn / 128, static_cast<float *>(work),
                      (int64_t)(work_bytes / (128 * 128 * 4)), std::min(max_parts, 255)};
     tmark("gemm_bf16x3_corr", s, true);
-    hipLaunchKernelGGL(correct_direct, dim3((unsigned)(2 * device_cu_count())), dim3(256), 0, s, g, p, fin);
+    hipLaunchKernelGGL(correct_direct, dim3((unsigned)(2 * device_cu_count())), dim3(256), 0, s, g, p);
     tmark("gemm_bf16x3_corr", s, false);
     return hipGetLastError();
 }

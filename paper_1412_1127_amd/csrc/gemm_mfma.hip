@@ -39,11 +39,10 @@ namespace {
 using namespace dev;
 
 // One thread per (unit, row, chunk): 8 consecutive K elements of one row.
-template <bool TRANS>
 __global__ __launch_bounds__(256) void pack_bf16x3(const float *__restrict__ X, int64_t R, int64_t K, int64_t ld,
                                                    char *__restrict__ out, int64_t nrb, int64_t nkb)
 {
-    pack_bf16x3_range<TRANS>(X, R, K, ld, out, nrb, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
+    pack_bf16x3_range(X, R, K, ld, out, nrb, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
                              (int64_t)gridDim.x * 256);
 }
 
@@ -309,7 +308,7 @@ __global__ __launch_bounds__(256) void pack_bf16x3_pair(const float *__restrict_
     if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0u;
     const int64_t nkb = (K + 31) / 32;
     if ((int)blockIdx.x < ga) {
-        pack_bf16x3_range<false>(A, M, K, lda, pa, (M + 31) / 32, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
+        pack_bf16x3_range(A, M, K, lda, pa, (M + 31) / 32, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
                                  (int64_t)ga * 256);
     } else {
         const int64_t b = blockIdx.x - ga;
@@ -807,7 +806,7 @@ hipError_t launch_pack_bf16x3(const float *x, int64_t rows, int64_t k, int64_t l
         hipLaunchKernelGGL(pack_bf16x3_t, dim3((unsigned)(cdiv(rows, TP_COLS) * BF_SPLIT * nkb)), dim3(256), 0, s, x,
                            rows, k, ld, static_cast<char *>(out), nrb, nkb, (int)cdiv(rows, TP_COLS));
     else
-        hipLaunchKernelGGL(pack_bf16x3<false>, dim3(grid), dim3(256), 0, s, x, rows, k, ld, static_cast<char *>(out),
+        hipLaunchKernelGGL(pack_bf16x3, dim3(grid), dim3(256), 0, s, x, rows, k, ld, static_cast<char *>(out),
                            nrb, nkb);
     tmark("pack_bf16x3", s, false);
     return hipGetLastError();

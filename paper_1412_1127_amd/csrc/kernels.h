@@ -205,10 +205,9 @@ hipError_t launch_gemm_i8_direct(const int32_t *a, const int32_t *b, int32_t *c,
 // three missing products on the tiles in the records' list (rec: one record
 // per tile of `tile`, 128 x 128 or larger), straight from the float32 operands
 // (lda, ldb <= DIRECT_MAX_LD).  work: work_bytes for partial sums (256-byte
-// aligned) of at most max_parts K parts per sub-tile.  fin: a co-scheduled reduction's last step, run by workgroup 0.
+// aligned) of at most max_parts K parts per sub-tile.
 hipError_t launch_correction(const float *a, const float *b, float *c, const GemmShape &sh, int tile, ProbeRecord *rec,
-                             void *work, size_t work_bytes, int max_parts, hipStream_t s,
-                             const RedFinal &fin = RedFinal());
+                             void *work, size_t work_bytes, int max_parts, hipStream_t s);
 // Rows and columns of a tile configuration (0: the size heuristic's).
 void tile_dims(int tile, int64_t m, int64_t n, int &bm, int &bn);
 
@@ -226,7 +225,7 @@ struct BatchMat {       // one matmul: operands, output, tiling
     const float *a, *b;
     float *c;
     int64_t len;
-    int32_t tile, tiles_m, tiles_n, products;
+    int32_t tile, tiles_m, tiles_n;
 };
 struct BatchRed {       // one reduction: input, chunking, result slot
     const float *x;

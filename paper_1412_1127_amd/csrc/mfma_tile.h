@@ -54,13 +54,9 @@ __device__ inline void split3(float x, uint16_t &h, uint16_t &m, uint16_t &l)
     l = bf16_bits((__bf16)r2);
 }
 
-// One thread per (unit, row, chunk): 8 consecutive K elements of one row.
-// TRANS = false: X is R x K row-major (operand row r = X row r), element
-//                (r, e) at X[r*ld + e].
-// TRANS = true:  X is K x R row-major (operand row r = X column r), element
-//                (e, r) at X[e*ld + r].
+// One thread per (unit, row, chunk): 8 consecutive K elements of one row of
+// X (R x K row-major: element (r, e) at X[r*ld + e]).
 // Work items id0, id0 + step, ... of one operand (128 items per unit).
-template <bool TRANS>
 __device__ __attribute__((always_inline)) inline void pack_bf16x3_range(const float *__restrict__ X, int64_t R,
                                                                         int64_t K, int64_t ld,
                                                                         char *__restrict__ out, int64_t nrb,
@@ -70,22 +66,12 @@ __device__ __attribute__((always_inline)) inline void pack_bf16x3_range(const fl
     for (int64_t id = id0; id < total; id += step) {
         const int64_t unit = id >> 7;
         const int w = (int)(id & 127);
-        int r, c;
-        if (TRANS) {
-            r = w & 31;
-            c = w >> 5;
-        } else {
-            r = w >> 2;
-            c = w & 3;
-        }
+        const int r = w >> 2, c = w & 3;
         const int64_t rb = unit / nkb, kb = unit - rb * nkb;
         const int64_t row = rb * 32 + r;
         const int64_t k0 = kb * 32 + c * 8;
         float v[8];
-        if (TRANS) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) v[t] = (row < R && k0 + t < K) ? X[(k0 + t) * ld + row] : 0.0f;
-        } else if (row < R && k0 + 8 <= K) {
+        if (row < R && k0 + 8 <= K) {
             const f32x4u *p = reinterpret_cast<const f32x4u *>(X + row * ld + k0);
             // read once: non-temporal, so that the stream keeps out of the caches
             const f32x4u a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);

@@ -2341,7 +2341,6 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
             m.c = static_cast<float *>(it.c);
             m.len = it.n;
             m.tile = batch_tile(it, kBatchDefaultThreshold, auto_prec);
-            m.products = products;
             mats.push_back(m);
             mat_item.push_back(i);
             max_tiles += ((it.n + 63) / 64) * ((it.n + 63) / 64);
