@@ -38,12 +38,22 @@ namespace {
 
 using namespace dev;
 
+// The rows of one operand, by how they are aligned (uniform).
+__device__ __attribute__((always_inline)) inline void pack_bf16x3_rows(const float *__restrict__ X, int64_t R, int64_t K,
+                                                                       int64_t ld, char *__restrict__ out, int64_t nrb,
+                                                                       int64_t nkb, int64_t id0, int64_t step)
+{
+    if (rows_aligned16(X, ld))
+        pack_bf16x3_range<true>(X, R, K, ld, out, nrb, nkb, id0, step);
+    else
+        pack_bf16x3_range<false>(X, R, K, ld, out, nrb, nkb, id0, step);
+}
+
 // One thread per (unit, row, chunk): 8 consecutive K elements of one row.
 __global__ __launch_bounds__(256) void pack_bf16x3(const float *__restrict__ X, int64_t R, int64_t K, int64_t ld,
                                                    char *__restrict__ out, int64_t nrb, int64_t nkb)
 {
-    pack_bf16x3_range(X, R, K, ld, out, nrb, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
-                             (int64_t)gridDim.x * 256);
+    pack_bf16x3_rows(X, R, K, ld, out, nrb, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
 
@@ -158,6 +168,7 @@ __device__ inline uint32_t pack_i8_items(const int32_t *__restrict__ X, int64_t 
 // fastest, so that consecutive wavefronts walk along the same rows; each
 // wavefront keeps NI items' loads in flight.  w0 / wstep: this wavefront's
 // first item and the number of wavefronts.  Returns the lane's max |x|.
+template <bool STREAM>
 __device__ inline uint32_t pack_i8_rows_one(const int32_t *__restrict__ X, int64_t R, int64_t K, int64_t ld,
                                             char *__restrict__ out, int64_t nrb, int64_t nkb, int pstride, int64_t w0,
                                             int64_t wstep)
@@ -178,7 +189,7 @@ __device__ inline uint32_t pack_i8_rows_one(const int32_t *__restrict__ X, int64
                 const int64_t row = rq * 4 + lr, k = kb * 64 + lk;
                 if (row < R) {
                     if (k + 4 <= K) {
-                        v[u] = __builtin_nontemporal_load(reinterpret_cast<const i32x4u *>(X + row * ld + k));
+                        v[u] = load_row4<STREAM>(reinterpret_cast<const i32x4u *>(X + row * ld + k));
                     } else {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
@@ -231,7 +242,8 @@ constexpr int TP_ROWS = 16;          // rows of X per tile
 constexpr int BF_SPLIT = 32 / TP_ROWS;  // tiles per 32-element bf16x3 K unit
 constexpr int I8_SPLIT = 64 / TP_ROWS;  // tiles per 64-element int8 K unit
 
-__device__ inline void stage_rows(const uint32_t *__restrict__ X, int64_t R, int64_t K, int64_t ld, int64_t k0,
+template <bool STREAM>
+__device__ inline void stage_rows_of(const uint32_t *__restrict__ X, int64_t R, int64_t K, int64_t ld, int64_t k0,
                                   int64_t c0, uint32_t (*t)[TP_COLS])
 {
     // TP_ROWS rows x 64 four-column groups, TP_ROWS / 4 per thread
@@ -243,7 +255,7 @@ __device__ inline void stage_rows(const uint32_t *__restrict__ X, int64_t R, int
         uint32_t w[4] = {0u, 0u, 0u, 0u};
         if (k < K) {
             if (col + 4 <= R) {
-                const u32x4u v = __builtin_nontemporal_load(reinterpret_cast<const u32x4u *>(X + k * ld + col));
+                const u32x4u v = load_row4<STREAM>(reinterpret_cast<const u32x4u *>(X + k * ld + col));
                 w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
             } else {
 #pragma unroll
@@ -253,6 +265,15 @@ __device__ inline void stage_rows(const uint32_t *__restrict__ X, int64_t R, int
         }
         *reinterpret_cast<u32x4_t *>(&t[row][c4]) = u32x4_t{w[0], w[1], w[2], w[3]};
     }
+}
+
+__device__ inline void stage_rows(const uint32_t *__restrict__ X, int64_t R, int64_t K, int64_t ld, int64_t k0,
+                                  int64_t c0, uint32_t (*t)[TP_COLS])
+{
+    if (rows_aligned16(X, ld))
+        stage_rows_of<true>(X, R, K, ld, k0, c0, t);
+    else
+        stage_rows_of<false>(X, R, K, ld, k0, c0, t);
 }
 
 // bf16x3 planes of B^T for column tile bx of X and part by % BF_SPLIT of
@@ -308,7 +329,7 @@ __global__ __launch_bounds__(256) void pack_bf16x3_pair(const float *__restrict_
     if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0u;
     const int64_t nkb = (K + 31) / 32;
     if ((int)blockIdx.x < ga) {
-        pack_bf16x3_range(A, M, K, lda, pa, (M + 31) / 32, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
+        pack_bf16x3_rows(A, M, K, lda, pa, (M + 31) / 32, nkb, (int64_t)blockIdx.x * 256 + threadIdx.x,
                                  (int64_t)ga * 256);
     } else {
         const int64_t b = blockIdx.x - ga;
@@ -407,7 +428,10 @@ __device__ inline uint32_t pack_i8_cols(const int32_t *__restrict__ X, int64_t R
     constexpr int CPT = TP_ROWS / 16;  // 16-element chunks per row per tile
     const int64_t kb = by / I8_SPLIT, rb0 = bx * (TP_COLS / 32);
     const int part = (int)(by % I8_SPLIT);
-    stage_rows(reinterpret_cast<const uint32_t *>(X), R, K, ld, kb * 64 + part * TP_ROWS, rb0 * 32, t);
+    if constexpr (ONE)
+        stage_rows(reinterpret_cast<const uint32_t *>(X), R, K, ld, kb * 64 + part * TP_ROWS, rb0 * 32, t);
+    else  // bound by its stores: one form of load for any rows (4097 x 4097: 48 us, 53 us with both)
+        stage_rows_of<true>(reinterpret_cast<const uint32_t *>(X), R, K, ld, kb * 64 + part * TP_ROWS, rb0 * 32, t);
     __syncthreads();
     uint32_t mx = 0;
     // 8 units x 32 rows x CPT chunks of 16 elements
@@ -477,9 +501,11 @@ __global__ __launch_bounds__(256) void pack_i8_pair(const int32_t *__restrict__ 
     const int64_t nkb = (K + 63) / 64;
     uint32_t mx = 0;
     if ((int)blockIdx.x < ga) {
+        const int64_t w0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), wstep = (int64_t)ga * 4;
         if constexpr (ONE)
-            mx = pack_i8_rows_one(A, M, K, lda, pa, (M + 31) / 32, nkb, pstride,
-                                  (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), (int64_t)ga * 4);
+            mx = rows_aligned16(A, lda)
+                     ? pack_i8_rows_one<true>(A, M, K, lda, pa, (M + 31) / 32, nkb, pstride, w0, wstep)
+                     : pack_i8_rows_one<false>(A, M, K, lda, pa, (M + 31) / 32, nkb, pstride, w0, wstep);
         else
             mx = pack_i8_items<false>(A, M, K, lda, pa, (M + 31) / 32, nkb, np, pstride,
                                       (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)ga * 256);
