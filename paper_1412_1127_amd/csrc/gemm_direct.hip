@@ -146,8 +146,13 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
 // C += the three correction products on the listed tiles: a persistent grid
 // over (marked tile, 128 x 128 sub-tile, K part).  How many tiles are marked is
 // known on the device only, and a few marked tiles must still fill the chip,
-// so the K parts per sub-tile follow from the count: about four units per
-// workgroup.  Parts leave their sums in `partials`, the last one (the record's
+// so the K parts per sub-tile follow from the count: at most about four units
+// per workgroup (more parts share fewer operands in the L2: all of LEN = 6144
+// marked 2.7 ms in one part, 2.96 in two), and of those the number whose last
+// round of units leaves the least of the grid idle (LEN = 4096, row-scaled, 92
+// sub-tiles: five parts in one round 474 us a call, eight in two 511, packed
+// 64 x 64 correction 492; 20 % of LEN = 6144 marked, 468 sub-tiles, one part
+// 1.57 ms, five 1.78).  Parts leave their sums in `partials`, the last one (the record's
 // ticket) adds them in part order to C; the result does not depend on the
 // list's order.  Before, every 64 x 64 sub-tile of C had a workgroup that read
 // its record and, if marked, ran the packed three-plane tile over all of K:
@@ -173,9 +178,13 @@ __global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan 
     if (count == 0) return;
     const int subs = c.subs_m * c.subs_n;
     const int64_t S = (int64_t)count * subs;
-    int64_t parts = min<int64_t>(min<int64_t>(c.max_parts, g.K / 256), (4 * (int64_t)gridDim.x + S - 1) / S);
-    parts = min<int64_t>(parts, c.cap / S);
-    if (parts < 1) parts = 1;
+    const int64_t most = min<int64_t>(min<int64_t>(min<int64_t>(c.max_parts, g.K / 256), c.cap / S),
+                                      (4 * (int64_t)gridDim.x + S - 1) / S);
+    int64_t parts = 1, rounds = (S + gridDim.x - 1) / gridDim.x;
+    for (int64_t q = 2; q <= most; ++q) {
+        const int64_t r = (S * q + gridDim.x - 1) / gridDim.x;
+        if (r * parts < rounds * q) parts = q, rounds = r;
+    }
     const int64_t kpart = ((g.K + parts - 1) / parts + KS - 1) / KS * KS;
     parts = (g.K + kpart - 1) / kpart;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
