@@ -50,7 +50,8 @@ template <int BM, int BN, int KS, int G, int NPROD, uint64_t PL, bool AUTO, int 
     return std::max(n, std::max((G - 1) * BM * BN * 4, (int)sizeof(DirectProbeLds)));
 }
 
-// KS, G: the pass's stage and groups; KSC, GC: the correction's.
+// KS, G: the pass's stage and groups; KSC, GC: the correction's (GC 0: marked
+// tiles are left to a launch of their own).
 template <int BM, int BN, int KS, int G, int NPROD, uint64_t PL, bool AUTO, int KSC = KS, int GC = G>
 __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan pl)
 {
@@ -126,18 +127,22 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
                                         probe_block(id, (int)min<int64_t>(BN, g.N - col0), 1), L.c);
             direct_store<BM, BN, 2, 2>(g, tm, tn, t, acc.tile, false);
         }
-        if (!probe_direct<256 * G>(g, BM, BN, id, tm, tn, pl.tau2, pl.rec + id, L)) return;
-        // marked: C += the three correction products (by the threads that
-        // stored C, so each reads back its own elements)
-        __syncthreads();
-        int64_t b = g.K, e = g.K, b0, e0;
-        int barriers;
-        group_range<KSC, GC>(0, g.K, gi, b0, e0, barriers);
-        if (gi < GC) b = b0, e = e0;
-        direct_acc<BM, BN, KSC, 2, 2, 3, PL_CORR3>(
-            g, tm, tn, b, e, t, barriers, lds + (gi % GC) * direct_lds_bytes<BM, BN, KSC, 3, PL_CORR3>(), acc.tile);
-        group_sum<GC, 4>(acc.flat, gi < GC ? gi : -1, t, lds);
-        if (gi == 0) direct_store<BM, BN, 2, 2>(g, tm, tn, t, acc.tile, true);
+        if constexpr (GC == 0) {
+            (void)probe_direct<256 * G>(g, BM, BN, id, tm, tn, pl.tau2, pl.rec + id, L);
+        } else {
+            if (!probe_direct<256 * G>(g, BM, BN, id, tm, tn, pl.tau2, pl.rec + id, L)) return;
+            // C += the three correction products (by the threads that stored
+            // C, so each reads back its own elements)
+            __syncthreads();
+            int64_t b = g.K, e = g.K, b0, e0;
+            int barriers;
+            group_range<KSC, GC>(0, g.K, gi, b0, e0, barriers);
+            if (gi < GC) b = b0, e = e0;
+            direct_acc<BM, BN, KSC, 2, 2, 3, PL_CORR3>(
+                g, tm, tn, b, e, t, barriers, lds + (gi % GC) * direct_lds_bytes<BM, BN, KSC, 3, PL_CORR3>(), acc.tile);
+            group_sum<GC, 4>(acc.flat, gi < GC ? gi : -1, t, lds);
+            if (gi == 0) direct_store<BM, BN, 2, 2>(g, tm, tn, t, acc.tile, true);
+        }
     } else {
         if (gi == 0) direct_store<BM, BN, 2, 2>(g, tm, tn, t, acc.tile, false);
     }
@@ -160,8 +165,11 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
 // the row-scaled LEN = 8192 inputs (69 of 1024 tiles marked, 222 GFLOP); now
 // 0.46 ms.  The split into three planes bounds it (88 vector instructions for
 // 12 matrix instructions of a wavefront and 16 k).
+// After the direct kernel in more than one round of tiles there is no list:
+// every workgroup makes it from the records, in the order of the tiles.
 struct CorrPlan {
     ProbeRecord *rec;
+    int scan;           // > 0: no list, search this many records
     int tiles_n;        // marked tiles per row of C
     int subs_m, subs_n; // 128 x 128 sub-tiles of a marked tile
     float *partials;
@@ -174,8 +182,46 @@ __global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan 
     constexpr int BM = 128, KS = 16, NBLK = 4, WORDS = BM * BM;
     __shared__ __attribute__((aligned(1024))) char lds[direct_lds_bytes<BM, BM, KS, 3, PL_CORR3>()];
     __shared__ int last_part;
-    const int count = __builtin_amdgcn_readfirstlane(c.rec[0].count);
-    if (count == 0) return;
+    __shared__ int found[CORR_SCAN], nfound[4];
+    int count;
+    if (c.scan > 0) {
+        // wavefront w takes the w-th quarter of the records
+        constexpr int EACH = CORR_SCAN / 256;
+        const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+        int mine[EACH], n = 0;
+#pragma unroll
+        for (int q = 0; q < EACH; ++q) {
+            const int id = (w * EACH + q) * 64 + l;
+            mine[q] = id < c.scan ? c.rec[id].corrected : 0;
+        }
+        uint64_t ballot[EACH];
+#pragma unroll
+        for (int q = 0; q < EACH; ++q) {
+            ballot[q] = __ballot(mine[q] != 0);
+            n += __popcll(ballot[q]);
+        }
+        if (l == 0) nfound[w] = n;
+        __syncthreads();
+        int at = 0;
+        count = 0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (v < w) at += nfound[v];
+            count += nfound[v];
+        }
+        count = __builtin_amdgcn_readfirstlane(count);
+        if (count == 0) return;
+#pragma unroll
+        for (int q = 0; q < EACH; ++q) {
+            if (mine[q] != 0)
+                found[at + __popcll(ballot[q] & (((uint64_t)1 << l) - 1))] = (w * EACH + q) * 64 + l;
+            at += __popcll(ballot[q]);
+        }
+        __syncthreads();
+    } else {
+        count = __builtin_amdgcn_readfirstlane(c.rec[0].count);
+        if (count == 0) return;
+    }
     const int subs = c.subs_m * c.subs_n;
     const int64_t S = (int64_t)count * subs;
     const int64_t most = min<int64_t>(min<int64_t>(min<int64_t>(c.max_parts, g.K / 256), c.cap / S),
@@ -191,7 +237,7 @@ __global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan 
     for (int64_t u = blockIdx.x; u < S * parts; u += gridDim.x) {
         const int64_t x = u / parts, part = u % parts;
         const int sub = (int)(x % subs);
-        const int tile = __builtin_amdgcn_readfirstlane(c.rec[x / subs].mark);
+        const int tile = __builtin_amdgcn_readfirstlane(c.scan > 0 ? found[x / subs] : c.rec[x / subs].mark);
         const int tm = tile / c.tiles_n * c.subs_m + sub / c.subs_n, tn = tile % c.tiles_n * c.subs_n + sub % c.subs_n;
         if ((int64_t)tm * BM >= g.M || (int64_t)tn * BM >= g.N) continue;
         f32x16 acc[2][2];
@@ -247,13 +293,15 @@ hipError_t launch(const DirectArgs &g, const DirectPlan &pl, hipStream_t s)
 }  // namespace
 
 hipError_t launch_correction(const float *a, const float *b, float *c, const GemmShape &sh, int tile, ProbeRecord *rec,
-                             void *work, size_t work_bytes, int max_parts, hipStream_t s)
+                             void *work, size_t work_bytes, int max_parts, bool listed, hipStream_t s)
 {
     int bm, bn;
     tile_dims(tile, sh.m, sh.n, bm, bn);
     if (bm % 128 || bn % 128) return hipErrorInvalidValue;
+    const int scan = listed ? 0 : probe_tiles(tile, sh.m, sh.n);
+    if (scan > CORR_SCAN) return hipErrorInvalidValue;
     const DirectArgs g{a, b, c, sh.m, sh.n, sh.k, sh.lda, sh.ldb, sh.ldc};
-    const CorrPlan p{rec, (int)((sh.n + bn - 1) / bn), bm / 128, bn / 128, static_cast<float *>(work),
+    const CorrPlan p{rec, scan, (int)((sh.n + bn - 1) / bn), bm / 128, bn / 128, static_cast<float *>(work),
                      (int64_t)(work_bytes / (128 * 128 * 4)), std::min(max_parts, 255)};
     tmark("gemm_bf16x3_corr", s, true);
     hipLaunchKernelGGL(correct_direct, dim3((unsigned)(2 * device_cu_count())), dim3(256), 0, s, g, p);
@@ -262,7 +310,7 @@ hipError_t launch_correction(const float *a, const float *b, float *c, const Gem
 }
 
 hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
-                              double tau, ProbeRecord *rec, hipStream_t s, const SplitK &sk)
+                              double tau, ProbeRecord *rec, bool corrects, hipStream_t s, const SplitK &sk)
 {
     if (sh.m <= 0 || sh.n <= 0) return hipSuccess;
     int bm, bn;
@@ -290,8 +338,10 @@ hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const Ge
     tmark(name, s, true);
     hipError_t e = hipErrorInvalidValue;
     if (tile == GEMM_TILE_128) {
-        if (rec)
+        if (rec && corrects)
             e = launch<128, 128, 32, 2, 3, PL_CHEAP3, true, 16, 2>(g, pl, s);
+        else if (rec)
+            e = launch<128, 128, 32, 2, 3, PL_CHEAP3, true, 16, 0>(g, pl, s);
         else if (products == 6)
             e = launch<128, 128, 16, 2, 6, PL_FULL6, false>(g, pl, s);
         else if (products == 5)
@@ -299,7 +349,7 @@ hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const Ge
         else if (products == 3)
             e = launch<128, 128, 32, 2, 3, PL_CHEAP3, false>(g, pl, s);
     } else if (tile == GEMM_TILE_64) {
-        if (rec)
+        if (rec && corrects)
             e = launch<64, 64, 32, 4, 3, PL_CHEAP3, true, 32, 2>(g, pl, s);
         else if (products == 6)
             e = launch<64, 64, 32, 2, 6, PL_FULL6, false>(g, pl, s);

@@ -190,24 +190,27 @@ hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t s);
 // C = A B in one launch with no packed operands, on 64 x 64 or 128 x 128
 // tiles (tile); products as above (6, 5 or 3).  rec non-null: the AUTO steps
 // (three products, float64 probe of each tile with threshold tau into rec,
-// correction of the marked ones) in the same launch.  sk.parts > 1: the K
+// and, if corrects, correction of the marked ones; without it 128 x 128 tiles
+// only) in the same launch.  sk.parts > 1: the K
 // range in that many workgroups per tile, with split_k_bytes(tile, ...) of
 // workspace.  lda and ldb at most DIRECT_MAX_LD (32-bit offsets in a tile).
 constexpr int64_t DIRECT_MAX_LD = (int64_t)1 << 19;
 hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
-                              double tau, ProbeRecord *rec, hipStream_t s, const SplitK &sk = SplitK());
+                              double tau, ProbeRecord *rec, bool corrects, hipStream_t s, const SplitK &sk = SplitK());
 // int32: C = A B modulo 2^32 in one launch straight from the operands, with
 // as many int8 digits as each stage of the K loop needs (gemm_i8_direct.hip);
 // tile 64 x 64 or 128 x 128, sk, lda and ldb as above.
 hipError_t launch_gemm_i8_direct(const int32_t *a, const int32_t *b, int32_t *c, const GemmShape &sh, int tile,
                                  hipStream_t s, const SplitK &sk = SplitK());
-// The correction after a packed three-product pass and its probe: C += the
-// three missing products on the tiles in the records' list (rec: one record
-// per tile of `tile`, 128 x 128 or larger), straight from the float32 operands
+// The correction after a three-product pass and its probe: C += the three
+// missing products on the marked tiles, those in the records' list if listed,
+// else (at most CORR_SCAN records) those whose record says so (rec: one record per
+// tile of `tile`, 128 x 128 or larger), straight from the float32 operands
 // (lda, ldb <= DIRECT_MAX_LD).  work: work_bytes for partial sums (256-byte
 // aligned) of at most max_parts K parts per sub-tile.
+constexpr int CORR_SCAN = 1024;
 hipError_t launch_correction(const float *a, const float *b, float *c, const GemmShape &sh, int tile, ProbeRecord *rec,
-                             void *work, size_t work_bytes, int max_parts, hipStream_t s);
+                             void *work, size_t work_bytes, int max_parts, bool listed, hipStream_t s);
 // Rows and columns of a tile configuration (0: the size heuristic's).
 void tile_dims(int tile, int64_t m, int64_t n, int &bm, int &bn);
 

@@ -711,10 +711,19 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
         dk.parts = dc.parts;
         dk.work = work;
         auto *rec = prec == ACC_PREC_AUTO ? reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh)) : nullptr;
-        return check_launch(accx::launch_gemm_direct(a, b, c, sh,
-                                                     prec == ACC_PREC_FULL6 ? 6 : prec == ACC_PREC_FIVE ? 5 : 3, dc.tile,
-                                                     probe_tau(), rec, s, dk),
-                            "gemm (bf16x3, direct) launch");
+        // A marked tile of the last round, corrected by its own workgroup,
+        // keeps the rest of the chip waiting (20 of 361 tiles of LEN = 2338:
+        // 127 -> 213 us a call); a launch of its own shares the marked tiles'
+        // work among all CUs.  It costs 3 us where no tile is marked, too much
+        // for one round.
+        const int tiles = accx::probe_tiles(dc.tile, sh.m, sh.n);
+        const bool later = rec && dc.tile == accx::GEMM_TILE_128 && sh.k > 0 && tiles > accx::device_cu_count() &&
+                           tiles <= accx::CORR_SCAN;
+        hipError_t e = accx::launch_gemm_direct(a, b, c, sh, prec == ACC_PREC_FULL6 ? 6 : prec == ACC_PREC_FIVE ? 5 : 3,
+                                                dc.tile, probe_tau(), rec, !later, s, dk);
+        if (e == hipSuccess && later)
+            e = accx::launch_correction(a, b, c, sh, dc.tile, rec, work, packed_pair(sh, 2, 3), 8, false, s);
+        return check_launch(e, "gemm (bf16x3, direct) launch");
     }
     const size_t pb = accx::packed_bytes(sh.m, sh.k, 2, 3);
     char *pa = work, *pbt = work + pb;
@@ -747,7 +756,7 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
         if (e == hipSuccess)
             // (a forced tile is corrected in one K part: the sums of a batch)
             e = listed ? accx::launch_correction(a, b, c, sh, ptile, rec, work, packed_pair(sh, 2, 3),
-                                                 (flags & ACC_TILE_MASK) ? 1 : 8, s)
+                                                 (flags & ACC_TILE_MASK) ? 1 : 8, true, s)
                        : accx::launch_gemm_bf16x3(pa, pbt, c, sh, -3, true, accx::GEMM_TILE_64, s, rec, accx::SplitK(),
                                                   ptile);
         return check_launch(e, "gemm (bf16x3, probed) launch");
