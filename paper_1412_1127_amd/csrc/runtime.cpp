@@ -694,7 +694,7 @@ bool reads_operands(const void *a, const void *b, const void *c, const GemmShape
 acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmShape &sh, uint32_t flags, char *work,
                          size_t work_bytes, hipStream_t s, const CoReduce *red = nullptr)
 {
-    accx::SplitK sk = split_for(ACC_FLOAT32, sh, flags, work, work_bytes);
+    const accx::SplitK sk = split_for(ACC_FLOAT32, sh, flags, work, work_bytes);
     if (is_f32mm(flags)) {
         char *pa = work, *pbt = work + accx::packed_bytes(sh.m, sh.k, 4, 1);
         hipError_t e = accx::launch_pack_f32_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s);
@@ -730,14 +730,19 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     auto *rec = reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh));
     // the correction from the float32 operands, over the probe's list of
     // marked tiles; else the packed one, which looks at every tile's record
-    int ptile = 0;
+    int tile = 0, ptile = 0;
     bool listed = false;
     if (prec == ACC_PREC_AUTO) {
-        // The tile is made concrete here: the correction reads the probe's
-        // records in the layout of this tile, which must not be left to a
-        // default that each launch would resolve on its own.
-        ptile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
-        if (!ptile) ptile = dc.tile ? dc.tile : accx::default_tile(sh.m, sh.n);
+        // The tiles are made concrete here: the correction reads the probe's
+        // records in the layout of its tile, which must not be left to a
+        // default that each launch would resolve on its own.  Operands that
+        // the direct path does not take are probed on its tile all the same
+        // (the records' layout depends on the shape alone); their pass has
+        // the tile, and the split K, of any packed product.
+        tile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
+        ptile = tile ? tile : dc.tile;
+        if (!tile) tile = accx::default_tile(sh.m, sh.n);
+        if (!ptile) ptile = tile;
         listed = ptile != accx::GEMM_TILE_64 && sh.k > 0 && reads;
     }
     hipError_t e = accx::launch_pack_bf16x3_pair(a, sh.m, sh.lda, b, sh.n, sh.ldb, sh.k, pa, pbt, s,
@@ -746,10 +751,7 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     if (prec == ACC_PREC_AUTO) {
         // cheap pass, float64 probe per tile, then the three missing products
         // on the tiles the probe marked.
-        // Operands the direct path does not take: its tile (the records'
-        // layout depends on the shape alone), unsplit.
-        if (dc.tile) sk = accx::SplitK();
-        e = cheap_pass(pa, pbt, c, sh, ptile, sk, red, s);
+        e = cheap_pass(pa, pbt, c, sh, tile, sk, red, s);
         accx::RedFinal fin;
         if (red) fin = accx::RedFinal{red->part, red->parts, red->init, red->result};
         if (e == hipSuccess) e = accx::launch_probe_f64(pa, pbt, c, sh, ptile, probe_tau(), rec, listed, s, fin);

@@ -87,3 +87,45 @@ def test_c_in_the_padding_of_a(ax, kind):
     out = ac.cpu().numpy()
     assert np.array_equal(out[:, :k], a)
     _check(out[:, k:], a, b)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "marked"])
+@pytest.mark.parametrize("m,n,k", [(70, 50, 2049), (130, 200, 1500), (100, 1100, 300)])
+def test_rows_too_long_for_the_direct_path(ax, m, n, k, kind):
+    # rows further apart than the direct kernels' offsets reach: packed, on the
+    # tile and with the split K of the three-product call, so that the
+    # two agree bit for bit on unmarked tiles; marked ones are corrected
+    import torch
+    lda = (1 << 19) + 8
+    g = synth.rng(SEED, 97)
+    if kind == "marked":
+        a, b = _biased(g, (m, k)), _biased(g, (k, n))
+    else:
+        a, b = synth.uniform_pm1_f32((m, k), SEED, 9420), synth.uniform_pm1_f32((k, n), SEED, 9421)
+    buf = torch.zeros((m - 1) * lda + k, device="cuda")
+    buf.as_strided((m, k), (lda, 1)).copy_(torch.from_numpy(a))
+    db = torch.from_numpy(b).cuda()
+    fl = ax.ACC_KERNEL_TILED | ax.ACC_PREC_AUTO
+    ws = ax.accx_gemm_workspace_size(ax.ACC_FLOAT32, m, n, k, fl)
+    off, cnt = ax.accx_gemm_probe_layout(m, n, k, fl)
+    work = torch.full((ws,), 0xFF, dtype=torch.uint8, device="cuda")
+    out = []
+    for flags in (fl, ax.ACC_KERNEL_TILED | ax.ACC_PREC_CHEAP3):
+        dc = torch.full((m, n), float("nan"), device="cuda")
+        print("long rows m=%d n=%d k=%d %s flags=%#x" % (m, n, k, kind, flags), flush=True)
+        ax.accx_gemm_dev(ax.ACC_FLOAT32, m, n, k, buf, lda, db, n, dc, n, flags, work if flags == fl else None,
+                         ws if flags == fl else 0)
+        torch.cuda.synchronize()
+        out.append(dc.cpu().numpy())
+    recs = ax.probe_records(work[off:off + cnt * 608].cpu().numpy().tobytes(), cnt)
+    assert rel_fro(out[0], oracle.gemm(a, b)) <= FP32_REL_FRO_TOL
+    edge = next(e for e in (64, 128) if -(-m // e) * -(-n // e) == cnt)
+    nt = -(-n // edge)
+    if kind == "marked":
+        assert all(r.corrected for r in recs)
+    else:
+        # (a sampled error of this kind of values is rarely above the threshold)
+        assert sum(r.corrected for r in recs) <= cnt // 4
+    for q, r in enumerate(recs):
+        at = np.s_[q // nt * edge:(q // nt + 1) * edge, q % nt * edge:(q % nt + 1) * edge]
+        assert np.array_equal(out[0][at], out[1][at]) == (not r.corrected)
