@@ -2214,14 +2214,14 @@ void batch_tile_dims(int tile, int &bm, int &bn)
 }
 
 // Tile policy of a batch: an item's forced tile, else 64 x 64 when its LEN
-// is below `threshold`, else 128 x 128 or (AUTO batches) 256 x 128, whichever
-// covers the result at the lower cost, padding included.
-int batch_tile(const accx_batch_item &it, int64_t threshold, bool auto_prec)
+// is below `threshold`, else 128 x 128 or (wide) 256 x 128, whichever covers
+// the result at the lower cost, padding included.
+int batch_tile(const accx_batch_item &it, int64_t threshold, bool wide)
 {
     const int forced = (int)((it.flags & ACC_TILE_MASK) >> ACC_TILE_SHIFT);
     if (forced) return forced;
     if (it.n < threshold) return accx::GEMM_TILE_64;
-    if (!auto_prec) return accx::GEMM_TILE_128;
+    if (!wide) return accx::GEMM_TILE_128;
     const int64_t t128 = (it.n + 127) / 128, t256 = (it.n + 255) / 256;
     return 2.0 * t256 * t128 * batch_tile_cost(accx::GEMM_TILE_256x128) <
                    1.0 * t128 * t128 * batch_tile_cost(accx::GEMM_TILE_128)
@@ -2230,6 +2230,25 @@ int batch_tile(const accx_batch_item &it, int64_t threshold, bool auto_prec)
 }
 
 constexpr int64_t kBatchDefaultThreshold = 512;
+
+// Tiles the batch's matmuls (items[index[k]] for mats[k]): 256 x 128 tiles in
+// AUTO batches only, and only where the batch has more of them than three
+// quarters of the persistent workgroups; fewer leave workgroups idle that
+// 128 x 128 tiles keep busy.  us a launch, 256 x 128 / 128 x 128, AUTO: 2 x
+// LEN 2048 (256 tiles of 512 workgroups) 217 / 148, 8 x 1024 (256) 111 / 85,
+// 3 x 2048 (384) 227 / 208, 1 x 3584 (392) 365 / 396, 16 x 1024 (512) 133 /
+// 148, 4 x 2048 (512) 230 / 265, 5 x 2048 (640) 313 / 317, 24 x 1024 (768) 188 /
+// 209.
+void batch_tiles(std::vector<accx::BatchMat> &mats, const accx_batch_item *items, const std::vector<int> &index,
+                 int64_t threshold, bool auto_prec)
+{
+    int64_t wide = 0;
+    for (size_t k = 0; auto_prec && k < mats.size(); ++k)
+        if (batch_tile(items[index[k]], threshold, true) == accx::GEMM_TILE_256x128)
+            wide += ((mats[k].len + 255) / 256) * ((mats[k].len + 127) / 128);
+    const bool use = 4 * wide > 3 * (int64_t)accx::batch_workgroups();
+    for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[index[k]], threshold, use);
+}
 
 // Work queues for the given tiles, one per XCD (first[x] .. first[x + 1] of
 // the returned units).  A matmul goes whole to one queue, so that its tiles
@@ -2351,7 +2370,6 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
             m.b = static_cast<const float *>(it.b);
             m.c = static_cast<float *>(it.c);
             m.len = it.n;
-            m.tile = batch_tile(it, kBatchDefaultThreshold, auto_prec);
             mats.push_back(m);
             mat_item.push_back(i);
             max_tiles += ((it.n + 63) / 64) * ((it.n + 63) / 64);
@@ -2379,6 +2397,7 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         }
     }
     if (max_tiles + info.chunks >= (int64_t)0x7fffffff) return fail(ACC_ERR_INVALID_ARG, "batch too large");
+    batch_tiles(mats, items, mat_item, kBatchDefaultThreshold, auto_prec);
     uint32_t first[accx::BATCH_QUEUES + 1];
     std::vector<accx::BatchUnit> units = batch_units(mats, reds, first);
     const size_t max_units = (size_t)(max_tiles + info.chunks);
@@ -2493,7 +2512,7 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         const int64_t cand[] = {0, 192, 320, 448, 576, 768, 65537};
         for (int64_t th : cand) {
             if (e != hipSuccess) break;
-            for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[mat_item[k]], th, auto_prec);
+            batch_tiles(mats, items, mat_item, th, auto_prec);
             std::vector<accx::BatchUnit> u = batch_units(mats, reds, b->queue.first);
             e = hipMemcpy(base + o_mats, mats.data(), sizeof(accx::BatchMat) * mats.size(), hipMemcpyHostToDevice);
             if (e == hipSuccess)
@@ -2519,7 +2538,7 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         if (cs) (void)hipStreamDestroy(cs);
         cs = nullptr;
         if (e == hipSuccess) {
-            for (size_t k = 0; k < mats.size(); ++k) mats[k].tile = batch_tile(items[mat_item[k]], threshold, auto_prec);
+            batch_tiles(mats, items, mat_item, threshold, auto_prec);
             units = batch_units(mats, reds, b->queue.first);
             e = hipMemcpy(base + o_mats, mats.data(), sizeof(accx::BatchMat) * mats.size(), hipMemcpyHostToDevice);
             if (e == hipSuccess)
