@@ -706,7 +706,7 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
     const DirectChoice dc = direct_choice(sh, flags);
     const uint32_t prec = flags & ACC_PREC_MASK;
     const bool reads = reads_operands(a, b, c, sh);
-    if (dc.tile && reads) {
+    if (dc.tile && reads && !red) {
         accx::SplitK dk;
         dk.parts = dc.parts;
         dk.work = work;
@@ -1736,6 +1736,9 @@ MatRedPlan matred_plan(const GemmShape &sh, uint32_t flags, int64_t n, const voi
     int tile = resolve_tile(ACC_FLOAT32, sh, (flags & ~ACC_PREC_MASK) | ACC_PREC_CHEAP3, 0);
     if (!tile) tile = accx::default_tile(sh.m, sh.n);
     if (tile != accx::GEMM_TILE_256 || split_plan(ACC_FLOAT32, sh, flags).parts > 1) return p;
+    // the direct path, which run_tiled_f32 tries first, carries no sum (a
+    // result with a 256 x 256 tile for every CU is beyond its limit today)
+    if (direct_choice(sh, flags).tile) return p;
     p.fused = true;
     return p;
 }

@@ -1,0 +1,42 @@
+"""A matmul and a sum in one region on both sides of the lines between the
+direct path, the packed path and the co-scheduled pass: the sum is written on
+each of them, and the matrix is that of the matmul alone.  (Lines for 256
+compute units: 640 tiles of 128 x 128 at 3200, 256 of 256 x 256 at 3841.)"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", ["auto", "cheap3"])
+@pytest.mark.parametrize("length,kernel", [(1000, "direct"), (3200, "direct"), (3201, "packed"), (3840, "packed"),
+                                           (3841, "co-scheduled")])
+def test_sum_is_written(prec, length, kernel):
+    import torch
+
+    import paper_1412_1127_amd as ax
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("lines for 256 compute units")
+    ax.acc_init(0, 0)
+    flags = ax.ACC_KERNEL_TILED | (ax.ACC_PREC_AUTO if prec == "auto" else ax.ACC_PREC_CHEAP3)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    a, b = [torch.rand((length, length), generator=g, device="cuda") * 2 - 1 for _ in range(2)]
+    n = 3000001
+    x = torch.rand(n, generator=g, device="cuda")
+    c, alone = torch.full_like(a, float("nan")), torch.full_like(a, float("nan"))
+    res = torch.full((1,), float("nan"), device="cuda")
+    print("matmul+reduce lines len=%d %s" % (length, prec), flush=True)
+    ax.accx_timing_enable(True)
+    ax.accx_timing_read(reset=True)
+    ax.accx_matmul_reduce_dev(a, b, c, length, flags, x, n, 0.25, res)
+    torch.cuda.synchronize()
+    names = set(ax.accx_timing_read(reset=True))
+    ax.accx_timing_enable(False)
+    ax.accx_matmul_dev(ax.ACC_FLOAT32, a, b, alone, length, flags)
+    torch.cuda.synchronize()
+    want = float(x.sum(dtype=torch.float64)) + 0.25
+    assert abs(float(res) - want) <= 1e-5 * want
+    assert torch.equal(c, alone) and bool(torch.isfinite(c).all())
+    direct = bool(names & {"gemm_direct", "gemm_direct_auto"})
+    assert direct == (kernel == "direct") and ("reduce_fast" in names) == (kernel != "co-scheduled"), names
+    ax.acc_shutdown()
