@@ -545,10 +545,12 @@ int resolve_tile(int t, const GemmShape &sh, uint32_t flags, int limbs)
 // 128 x 128) 280 / 239, 3500 (3.1 rounds) 358 / 357; six products: 256 10.8 /
 // 7.5, 1000 29 / 19, 2048 105 / 89, 2200 (1.3 rounds) 165 / 165.  Beyond one
 // round the packed path's larger tiles win: 4096 x 4096 x 512 75 / 87.
-// Without the probe (CHEAP3) the packed path is two launches, and wins between
-// one and two rounds on long loops (2060 93 / 98, 2700 139 / 144, but 3072 241
-// / 219 and 9000 x 500 x 1000 66 / 55) and beyond one round on short ones
-// (3000 x 3000 x 16 20.0 / 22.1, 2040 x 2300 x 200 22.4 / 23.3).
+// Between one and 1.4 rounds the last round is nearly empty, which on long
+// loops costs more than the prepass (2169 x 2169 x 1800 102 / 108, 2269 x 2269
+// x 4756 230 / 255, but 2100 x 2100 x 1040 73 / 68 and 2400 x 2400 x 1344 87 /
+// 80).  Without the probe (CHEAP3) the packed path is two launches, and wins
+// up to two rounds (2060 93 / 98, 2100 x 2100 x 1040 53 / 55) and on short
+// loops (3000 x 3000 x 16 20.0 / 22.1), but not beyond (3072 241 / 219).
 // Among 64 x 64 tiles, 128 x 128 tiles and K parts the estimate below picks:
 // a base (launch, first loads, probe, stores), the same again, but for the
 // launch, for each further round, and a time per k and round, all fitted to
@@ -573,7 +575,8 @@ DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
     const int64_t cus = accx::device_cu_count();
     const int64_t t128 = ((sh.m + 127) / 128) * ((sh.n + 127) / 128), t64 = ((sh.m + 63) / 64) * ((sh.n + 63) / 64);
     if (2 * t128 > (three ? 5 : 2) * cus) return best;
-    if (prec == ACC_PREC_CHEAP3 && t128 > cus && (sh.k < 256 || (sh.k > 1024 && t128 <= 2 * cus))) return best;
+    if (probed && t128 > cus && 100 * t128 <= 142 * cus && sh.k > 1600) return best;
+    if (three && !probed && t128 > cus && (t128 <= 2 * cus || sh.k < 256)) return best;
     double best_us = 1e300;
     for (int tile : {accx::GEMM_TILE_64, accx::GEMM_TILE_128}) {
         const bool small = tile == accx::GEMM_TILE_64;

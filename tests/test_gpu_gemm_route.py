@@ -1,7 +1,7 @@
 """Which kernels a product of open tile runs on, on both sides of each
-line: short loops over several rounds of tiles on the larger tile, three
-products without a probe, and int32, on the packed path where it is the faster
-one; and the results there, against the oracle or float64.  (The lines depend on the number of
+line: short loops over several rounds of tiles on the larger tile, long loops
+in little more than one round, three products without a probe and int32 on the
+packed path where it is the faster one; and the results there, against the oracle or float64.  (The lines depend on the number of
 compute units; the sizes are those of 256.)"""
 import numpy as np
 import pytest
@@ -57,8 +57,10 @@ def test_tile_of_short_loops(ax, m, n, k, edge):
 
 
 @pytest.mark.parametrize("prec,m,n,k,direct", [
-    ("cheap3", 2048, 2048, 64, True), ("cheap3", 2060, 2060, 64, False), ("cheap3", 2060, 2060, 600, True),
-    ("cheap3", 2060, 2060, 1100, False), ("cheap3", 2950, 2950, 1100, True), ("cheap3", 3000, 3000, 64, False),
+    ("cheap3", 2048, 2048, 64, True), ("cheap3", 2060, 2060, 64, False), ("cheap3", 2060, 2060, 600, False),
+    ("cheap3", 2700, 2700, 1100, False), ("cheap3", 2950, 2950, 1100, True), ("cheap3", 3000, 3000, 64, False),
+    ("auto", 2048, 2048, 1700, True), ("auto", 2060, 2060, 1600, True), ("auto", 2060, 2060, 1601, False),
+    ("auto", 2400, 2400, 1700, False), ("auto", 2440, 2440, 1700, True),
     ("five", 2048, 2048, 128, True), ("five", 2060, 2060, 128, False), ("full6", 1030, 1030, 800, True), ("full6", 2048, 2048, 128, True),
     ("full6", 2060, 2060, 128, False)])
 def test_route(ax, prec, m, n, k, direct):
@@ -75,7 +77,10 @@ def test_route(ax, prec, m, n, k, direct):
     torch.cuda.synchronize()
     names = set(ax.accx_timing_read(reset=True))
     ax.accx_timing_enable(False)
-    assert names == ({"gemm_direct"} if direct else {"pack_bf16x3", "gemm_bf16x3"}), names
+    if prec == "auto":
+        assert ("gemm_direct_auto" in names) == direct and ("pack_bf16x3" in names) != direct, names
+    else:
+        assert names == ({"gemm_direct"} if direct else {"pack_bf16x3", "gemm_bf16x3"}), names
     ref = da.double() @ db.double()
     err = float((dc.double() - ref).norm() / ref.norm())
     assert err <= FP32_REL_FRO_TOL, err
