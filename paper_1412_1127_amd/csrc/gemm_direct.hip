@@ -155,9 +155,9 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
 // per workgroup (more parts share fewer operands in the L2: all of LEN = 6144
 // marked 2.7 ms in one part, 2.96 in two), and of those the number whose last
 // round of units leaves the least of the grid idle (LEN = 4096, row-scaled, 92
-// sub-tiles: five parts in one round 474 us a call, eight in two 511, packed
+// sub-tiles: five parts in one round 467 us a call, eight in two 37 more, packed
 // 64 x 64 correction 492; 20 % of LEN = 6144 marked, 468 sub-tiles, one part
-// 1.57 ms, five 1.78).  Parts leave their sums in `partials`, the last one (the record's
+// 1.57 ms, five 1.78), none shorter than 64.  Parts leave their sums in `partials`, the last one (the record's
 // ticket) adds them in part order to C; the result does not depend on the
 // list's order.  Before, every 64 x 64 sub-tile of C had a workgroup that read
 // its record and, if marked, ran the packed three-plane tile over all of K:
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan 
     }
     const int subs = c.subs_m * c.subs_n;
     const int64_t S = (int64_t)count * subs;
-    const int64_t most = min<int64_t>(min<int64_t>(min<int64_t>(c.max_parts, g.K / 256), c.cap / S),
+    const int64_t most = min<int64_t>(min<int64_t>(min<int64_t>(c.max_parts, g.K / 64), c.cap / S),
                                       (4 * (int64_t)gridDim.x + S - 1) / S);
     int64_t parts = 1, rounds = (S + gridDim.x - 1) / gridDim.x;
     for (int64_t q = 2; q <= most; ++q) {
@@ -262,20 +262,23 @@ __global__ __launch_bounds__(256, 2) void correct_direct(DirectArgs g, CorrPlan 
             const int last = last_part;
             __syncthreads();  // read by all before the next unit writes it
             if (!last) continue;
+            // a part's 64 words are all in flight at once (16 at a time, the
+            // sum of eight parts was a chain of 32 trips to memory)
             const float *p = c.partials + x * parts * WORDS + wave * (NBLK * 1024) + lane;
 #pragma unroll
-            for (int q = 0; q < NBLK; ++q) {
-                f32x16 sum = (f32x16)0;
-                for (int64_t d = 0; d < parts; ++d) {
-                    float w[16];
+            for (int q = 0; q < NBLK; ++q) acc[q / 2][q % 2] = (f32x16)0;
+            for (int64_t d = 0; d < parts; ++d) {
+                float w[NBLK][16];
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q)
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
-                        w[r] = __hip_atomic_load(p + d * WORDS + q * 1024 + r * 64, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
+                        w[q][r] = __hip_atomic_load(p + d * WORDS + q * 1024 + r * 64, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sum[r] += w[r];
-                }
-                acc[q / 2][q % 2] = sum;
+                for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[q / 2][q % 2][r] += w[q][r];
             }
         }
         direct_store<BM, BM, 2, 2>(g, tm, tn, threadIdx.x, acc, true);
