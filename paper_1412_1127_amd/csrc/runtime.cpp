@@ -715,12 +715,13 @@ acc_status run_tiled_f32(const float *a, const float *b, float *c, const GemmSha
         dk.work = work;
         auto *rec = prec == ACC_PREC_AUTO ? reinterpret_cast<accx::ProbeRecord *>(work + probe_offset(sh)) : nullptr;
         // A marked tile of the last round, corrected by its own workgroup,
-        // keeps the rest of the chip waiting (20 of 361 tiles of LEN = 2338:
-        // 127 -> 213 us a call); a launch of its own shares the marked tiles'
-        // work among all CUs.  It costs 3 us where no tile is marked, too much
-        // for one round.
+        // keeps the rest of the chip waiting, 37 ns per k; a launch of its own
+        // shares the marked tiles' work among all CUs (row-scaled LEN = 2500,
+        // 24 of 400 tiles: 228 -> 187 us a call).  It costs 2 us where no tile
+        // is marked, too much for one round or a short loop (3064 x 3064 x 126:
+        // 35.8 / 37.5).
         const int tiles = accx::probe_tiles(dc.tile, sh.m, sh.n);
-        const bool later = rec && dc.tile == accx::GEMM_TILE_128 && sh.k > 0 && tiles > accx::device_cu_count() &&
+        const bool later = rec && dc.tile == accx::GEMM_TILE_128 && sh.k >= 512 && tiles > accx::device_cu_count() &&
                            tiles <= accx::CORR_SCAN;
         hipError_t e = accx::launch_gemm_direct(a, b, c, sh, prec == ACC_PREC_FULL6 ? 6 : prec == ACC_PREC_FIVE ? 5 : 3,
                                                 dc.tile, probe_tau(), rec, !later, s, dk);

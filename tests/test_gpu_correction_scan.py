@@ -36,9 +36,10 @@ def _biased(g, shape):
 # 289, 576, 288 and 640 records (the most there are); rows of A that are
 # biased (a multiple of 128, or all), the others hold one bf16 term per
 # element, for which three products are exact
-@pytest.mark.parametrize("m,n,k,rows", [(2060, 2150, 300, 2060), (2060, 2150, 800, 128), (2060, 2150, 800, 1024),
-                                        (2060, 2150, 300, 0), (2950, 2950, 40, 2950), (9100, 500, 1100, 256),
-                                        (2550, 4090, 96, 2550), (2200, 2200, 1, 0)])
+@pytest.mark.parametrize("m,n,k,rows", [(2060, 2150, 600, 2060), (2060, 2150, 800, 128), (2060, 2150, 800, 1024),
+                                        (2060, 2150, 600, 0), (2950, 2950, 520, 2950), (9100, 500, 1100, 256),
+                                        (2550, 4090, 512, 2550), (2060, 2150, 511, 2060), (2950, 2950, 40, 384),
+                                        (2200, 2200, 1, 0)])
 def test_marked_tiles(ax, m, n, k, rows):
     import torch
     g = synth.rng(SEED, 96)
@@ -62,7 +63,8 @@ def test_marked_tiles(ax, m, n, k, rows):
         torch.cuda.synchronize()
         names = set(ax.accx_timing_read(reset=True))
         ax.accx_timing_enable(False)
-        assert names == {"gemm_direct_auto", "gemm_bf16x3_corr"}, names
+        # (short loops: each marked tile by the workgroup that found it)
+        assert names == {"gemm_direct_auto"} | ({"gemm_bf16x3_corr"} if k >= 512 else set()), names
         c = dc.cpu().numpy()
         assert rel_fro(c[:rows], ref[:rows]) <= FP32_REL_FRO_TOL
         assert rel_fro(c[rows:], ref[rows:]) <= FP32_REL_FRO_TOL
