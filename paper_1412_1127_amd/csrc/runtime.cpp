@@ -581,7 +581,7 @@ DirectChoice direct_choice(const GemmShape &sh, uint32_t flags)
     for (int tile : {accx::GEMM_TILE_64, accx::GEMM_TILE_128}) {
         const bool small = tile == accx::GEMM_TILE_64;
         const int64_t tiles = small ? t64 : t128;
-        const double base = small ? (three ? 7.0 : 5.5) : (three ? 9.5 : 8.5);
+        const double base = small ? (probed ? 7.0 : three ? 5.3 : 5.5) : (probed ? 9.5 : three ? 7.4 : 8.5);
         const double more = small ? (probed ? 5.0 : three ? 3.3 : 2.5) : (probed ? 6.9 : three ? 5.2 : 4.9);
         const double per_k = small ? (three ? 0.0127 : 0.0165) : (three ? 0.0296 : 0.045);
         for (int parts = 1; parts <= 8; ++parts) {
