@@ -35,42 +35,8 @@ namespace {
 template <typename L>
 __global__ __launch_bounds__(RT) void reduce_fast(const L *__restrict__ x, int64_t n, uint32_t *__restrict__ partials)
 {
-    using V = typename Vec<L>::T;
     __shared__ L lds4[4];
-
-    // Aligned body of 16-byte vectors, with up to 3 leading and 3 trailing
-    // scalars (x may start at any 4-byte boundary).
-    const uintptr_t addr = (uintptr_t)x;
-    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) >> 2);
-    if (head > n) head = n;
-    const int64_t nvec = (n - head) >> 2;
-    const int64_t tail0 = head + (nvec << 2);
-    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
-
-    const int64_t stride = (int64_t)gridDim.x * RT;
-    int64_t v = (int64_t)blockIdx.x * RT + threadIdx.x;
-    V acc[RU];
-#pragma unroll
-    for (int u = 0; u < RU; ++u) acc[u] = (V)0;
-    for (; v + (RU - 1) * stride < nvec; v += RU * stride) {
-        V t[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + v + u * stride);
-#pragma unroll
-        for (int u = 0; u < RU; ++u) acc[u] += t[u];
-    }
-    for (; v < nvec; v += stride) acc[0] += __builtin_nontemporal_load(xv + v);
-    // fixed pairwise combination of the accumulators
-#pragma unroll
-    for (int w = RU / 2; w > 0; w >>= 1)
-#pragma unroll
-        for (int u = 0; u < w; ++u) acc[u] += acc[u + w];
-    L s = hsum<L>(acc[0]);
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < head) s = s + x[threadIdx.x];
-        if ((int64_t)threadIdx.x < n - tail0) s = s + x[tail0 + threadIdx.x];
-    }
-    s = block_sum(s, lds4);
+    const L s = fast_partial(x, n, lds4);
     if (threadIdx.x == 0) partials[blockIdx.x] = to_bits(s);
 }
 
@@ -121,56 +87,10 @@ template <typename E, int NV, uint32_t SIG>
 __global__ __launch_bounds__(RT) void reduce_vars(const E *__restrict__ x, int64_t n, RedVars vars,
                                                   uint64_t *__restrict__ partials)
 {
-    using R = Red<E>;
-    using V = typename R::V;
-    constexpr int W = R::W;
     __shared__ E lds4[4];
-
-    int op[NV], sq[NV];
-    E acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        op[v] = SIG == SIG_RUNTIME ? vars.op[v] : (int)((SIG >> (4 * v)) & 3u);
-        sq[v] = SIG == SIG_RUNTIME ? vars.square[v] : (int)((SIG >> (4 * v + 2)) & 1u);
-        acc[v] = red_identity<E>(op[v]);
-    }
-    auto fold = [&](E t) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] = red_apply<E>(op[v], acc[v], sq[v] ? R::mul(t, t) : t);
-    };
-
-    // Aligned body of 16-byte vectors, up to W-1 leading and trailing scalars.
-    const uintptr_t addr = (uintptr_t)x;
-    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) / sizeof(E));
-    if (head > n) head = n;
-    const int64_t nvec = (n - head) / W;
-    const int64_t tail0 = head + nvec * W;
-    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
-    const int64_t stride = (int64_t)gridDim.x * RT;
-    int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x;
-    for (; i + (RU - 1) * stride < nvec; i += RU * stride) {
-        V t[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + i + u * stride);
-#pragma unroll
-        for (int u = 0; u < RU; ++u)
-#pragma unroll
-            for (int e = 0; e < W; ++e) fold(t[u][e]);
-    }
-    for (; i < nvec; i += stride) {
-        const V t = __builtin_nontemporal_load(xv + i);
-#pragma unroll
-        for (int e = 0; e < W; ++e) fold(t[e]);
-    }
-    if (blockIdx.x == 0) {
-        if ((int64_t)threadIdx.x < head) fold(x[threadIdx.x]);
-        if ((int64_t)threadIdx.x < n - tail0) fold(x[tail0 + threadIdx.x]);
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const E b = block_apply<E>(op[v], acc[v], lds4);
+    vars_partials<E, NV, SIG>(x, n, vars, lds4, [&](int v, int, E b) {
         if (threadIdx.x == 0) partials[(size_t)v * gridDim.x + blockIdx.x] = as_bits<E>(b);
-    }
+    });
 }
 
 // One workgroup folds the g partials of each variable in index order, then
@@ -284,44 +204,13 @@ hipError_t launch_reduce(const L *x, int64_t n, L init, L *result, void *work, b
     return hipGetLastError();
 }
 
-template <typename E, int NV, uint32_t SIG>
-void launch_sig(const E *x, int64_t n, const RedVars &vars, uint64_t *partials, unsigned g, hipStream_t s)
-{
-    hipLaunchKernelGGL((reduce_vars<E, NV, SIG>), dim3(g), dim3(RT), 0, s, x, n, vars, partials);
-}
-
-// Compiled operator sets: one variable (+, max, min; x or x*x), and the
-// pairs the paper's reduction loops use (SRAD's sum and sum of squares) or
-// that come as one (max and min); anything else decodes at run time.
 template <typename E, int NV>
 void launch_vars_nv(const E *x, int64_t n, const RedVars &vars, E *result, uint64_t *partials, unsigned g,
                     hipStream_t s)
 {
-    uint32_t sig = 0;
-    for (int v = 0; v < NV; ++v) sig |= (uint32_t)(vars.op[v] | (vars.square[v] ? 4 : 0)) << (4 * v);
-    bool done = true;
-    if constexpr (NV == 1) {
-        switch (sig) {
-        case 0x0: launch_sig<E, 1, 0x0>(x, n, vars, partials, g, s); break;
-        case 0x1: launch_sig<E, 1, 0x1>(x, n, vars, partials, g, s); break;
-        case 0x2: launch_sig<E, 1, 0x2>(x, n, vars, partials, g, s); break;
-        case 0x4: launch_sig<E, 1, 0x4>(x, n, vars, partials, g, s); break;
-        case 0x5: launch_sig<E, 1, 0x5>(x, n, vars, partials, g, s); break;
-        case 0x6: launch_sig<E, 1, 0x6>(x, n, vars, partials, g, s); break;
-        default: done = false;
-        }
-    } else if constexpr (NV == 2) {
-        switch (sig) {
-        case 0x40: launch_sig<E, 2, 0x40>(x, n, vars, partials, g, s); break;  // sum, sum of squares
-        case 0x04: launch_sig<E, 2, 0x04>(x, n, vars, partials, g, s); break;  // sum of squares, sum
-        case 0x21: launch_sig<E, 2, 0x21>(x, n, vars, partials, g, s); break;  // max, min
-        case 0x12: launch_sig<E, 2, 0x12>(x, n, vars, partials, g, s); break;  // min, max
-        default: done = false;
-        }
-    } else {
-        done = false;
-    }
-    if (!done) launch_sig<E, NV, SIG_RUNTIME>(x, n, vars, partials, g, s);
+    with_operators<NV>(vars, [&](auto sig) {
+        hipLaunchKernelGGL((reduce_vars<E, NV, decltype(sig)::value>), dim3(g), dim3(RT), 0, s, x, n, vars, partials);
+    });
     hipLaunchKernelGGL((reduce_vars_final<E, NV>), dim3(1), dim3(RT), 0, s, partials, g, vars, result);
 }
 

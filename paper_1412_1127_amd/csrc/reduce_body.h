@@ -1,7 +1,10 @@
-// What the streaming reductions of one and of two launches share: the
-// combination of values over a workgroup, the operators and element types.
+// What the streaming reductions of one and of two launches share: the loop
+// over the elements, the combination of values over a workgroup, the operators
+// and element types.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -45,6 +48,47 @@ __device__ inline uint32_t to_bits(uint32_t v) { return v; }
 template <typename L> __device__ inline L from_bits(uint32_t b);
 template <> __device__ inline float from_bits<float>(uint32_t b) { return __uint_as_float(b); }
 template <> __device__ inline uint32_t from_bits<uint32_t>(uint32_t b) { return b; }
+
+// A workgroup's partial of the sum over its grid-stride slice; valid in
+// thread 0.
+template <typename L> __device__ inline L fast_partial(const L *__restrict__ x, int64_t n, L *lds4)
+{
+    using V = typename Vec<L>::T;
+
+    // Aligned body of 16-byte vectors, with up to 3 leading and 3 trailing
+    // scalars (x may start at any 4-byte boundary).
+    const uintptr_t addr = (uintptr_t)x;
+    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) >> 2);
+    if (head > n) head = n;
+    const int64_t nvec = (n - head) >> 2;
+    const int64_t tail0 = head + (nvec << 2);
+    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
+
+    const int64_t stride = (int64_t)gridDim.x * RT;
+    int64_t v = (int64_t)blockIdx.x * RT + threadIdx.x;
+    V acc[RU];
+#pragma unroll
+    for (int u = 0; u < RU; ++u) acc[u] = (V)0;
+    for (; v + (RU - 1) * stride < nvec; v += RU * stride) {
+        V t[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + v + u * stride);
+#pragma unroll
+        for (int u = 0; u < RU; ++u) acc[u] += t[u];
+    }
+    for (; v < nvec; v += stride) acc[0] += __builtin_nontemporal_load(xv + v);
+    // fixed pairwise combination of the accumulators
+#pragma unroll
+    for (int w = RU / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int u = 0; u < w; ++u) acc[u] += acc[u + w];
+    L s = hsum<L>(acc[0]);
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < head) s = s + x[threadIdx.x];
+        if ((int64_t)threadIdx.x < n - tail0) s = s + x[tail0 + threadIdx.x];
+    }
+    return block_sum(s, lds4);
+}
 
 // ---- reduction variables of any operator and type --------------------------
 //
@@ -149,6 +193,87 @@ template <typename E> __device__ inline E block_apply(int op, E v, E *lds4)
 // the per-element operator selection then costs more VALU work than the
 // element's load: about 4.5 instead of 6.9 TB/s over 1 GiB).
 constexpr uint32_t SIG_RUNTIME = 0xffffffffu;
+
+// Hands a workgroup's partial of each variable over its grid-stride slice to
+// put(v, operator, partial), which stores thread 0's.
+template <typename E, int NV, uint32_t SIG, typename Put>
+__device__ inline void vars_partials(const E *__restrict__ x, int64_t n, const RedVars &vars, E *lds4, Put put)
+{
+    using R = Red<E>;
+    using V = typename R::V;
+    constexpr int W = R::W;
+
+    int op[NV], sq[NV];
+    E acc[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        op[v] = SIG == SIG_RUNTIME ? vars.op[v] : (int)((SIG >> (4 * v)) & 3u);
+        sq[v] = SIG == SIG_RUNTIME ? vars.square[v] : (int)((SIG >> (4 * v + 2)) & 1u);
+        acc[v] = red_identity<E>(op[v]);
+    }
+    auto fold = [&](E t) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] = red_apply<E>(op[v], acc[v], sq[v] ? R::mul(t, t) : t);
+    };
+
+    // Aligned body of 16-byte vectors, up to W-1 leading and trailing scalars.
+    const uintptr_t addr = (uintptr_t)x;
+    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) / sizeof(E));
+    if (head > n) head = n;
+    const int64_t nvec = (n - head) / W;
+    const int64_t tail0 = head + nvec * W;
+    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
+    const int64_t stride = (int64_t)gridDim.x * RT;
+    int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x;
+    for (; i + (RU - 1) * stride < nvec; i += RU * stride) {
+        V t[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + i + u * stride);
+#pragma unroll
+        for (int u = 0; u < RU; ++u)
+#pragma unroll
+            for (int e = 0; e < W; ++e) fold(t[u][e]);
+    }
+    for (; i < nvec; i += stride) {
+        const V t = __builtin_nontemporal_load(xv + i);
+#pragma unroll
+        for (int e = 0; e < W; ++e) fold(t[e]);
+    }
+    if (blockIdx.x == 0) {
+        if ((int64_t)threadIdx.x < head) fold(x[threadIdx.x]);
+        if ((int64_t)threadIdx.x < n - tail0) fold(x[tail0 + threadIdx.x]);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) put(v, op[v], block_apply<E>(op[v], acc[v], lds4));
+}
+
+// Operator sets that are compiled: one variable (+, max, min; x or x*x), and
+// the pairs the paper's reduction loops use (SRAD's sum and sum of squares)
+// or that come as one (max and min); anything else decodes at run time.
+// Calls launch with the set as an integral constant.
+template <int NV, typename Launch> void with_operators(const RedVars &vars, Launch launch)
+{
+    uint32_t sig = 0;
+    for (int v = 0; v < NV; ++v) sig |= (uint32_t)(vars.op[v] | (vars.square[v] ? 4 : 0)) << (4 * v);
+    if constexpr (NV == 1) {
+        switch (sig) {
+        case 0x0: return launch(std::integral_constant<uint32_t, 0x0>{});
+        case 0x1: return launch(std::integral_constant<uint32_t, 0x1>{});
+        case 0x2: return launch(std::integral_constant<uint32_t, 0x2>{});
+        case 0x4: return launch(std::integral_constant<uint32_t, 0x4>{});
+        case 0x5: return launch(std::integral_constant<uint32_t, 0x5>{});
+        case 0x6: return launch(std::integral_constant<uint32_t, 0x6>{});
+        }
+    } else if constexpr (NV == 2) {
+        switch (sig) {
+        case 0x40: return launch(std::integral_constant<uint32_t, 0x40>{});  // sum, sum of squares
+        case 0x04: return launch(std::integral_constant<uint32_t, 0x04>{});  // sum of squares, sum
+        case 0x21: return launch(std::integral_constant<uint32_t, 0x21>{});  // max, min
+        case 0x12: return launch(std::integral_constant<uint32_t, 0x12>{});  // min, max
+        }
+    }
+    launch(std::integral_constant<uint32_t, SIG_RUNTIME>{});
+}
 
 }  // namespace
 

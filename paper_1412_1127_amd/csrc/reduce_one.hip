@@ -1,14 +1,11 @@
 // Reductions in one launch: the workgroup whose partial arrives last adds all
 // of them, in index order as the second launch of reduce.hip does, so that
-// both give the same bits.  (A file of its own, with its own copy of the
-// loops: the kernels of reduce.hip, whose code depends on what stands beside
-// it, took 16.7 us over 2^24 floats with two variables as they are and 17.0
-// in every form that shared a file or the loops with these.)
+// both give the same bits.  The loops over the elements are those of
+// reduce.hip's kernels (reduce_body.h).
 #include <hip/hip_runtime.h>
 
 #include <atomic>
 #include <chrono>
-#include <type_traits>
 
 #include "kernels.h"
 #include "reduce_body.h"
@@ -69,46 +66,6 @@ __device__ inline bool arrives_last(uint64_t *words, uint64_t number, unsigned g
     return last;
 }
 
-// A workgroup's partial sum, the steps of reduce_fast; valid in thread 0.
-template <typename L> __device__ inline L fast_partial(const L *__restrict__ x, int64_t n, L *lds4)
-{
-    using V = typename Vec<L>::T;
-
-    // Aligned body of 16-byte vectors, with up to 3 leading and 3 trailing
-    // scalars (x may start at any 4-byte boundary).
-    const uintptr_t addr = (uintptr_t)x;
-    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) >> 2);
-    if (head > n) head = n;
-    const int64_t nvec = (n - head) >> 2;
-    const int64_t tail0 = head + (nvec << 2);
-    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
-
-    const int64_t stride = (int64_t)gridDim.x * RT;
-    int64_t v = (int64_t)blockIdx.x * RT + threadIdx.x;
-    V acc[RU];
-#pragma unroll
-    for (int u = 0; u < RU; ++u) acc[u] = (V)0;
-    for (; v + (RU - 1) * stride < nvec; v += RU * stride) {
-        V t[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + v + u * stride);
-#pragma unroll
-        for (int u = 0; u < RU; ++u) acc[u] += t[u];
-    }
-    for (; v < nvec; v += stride) acc[0] += __builtin_nontemporal_load(xv + v);
-    // fixed pairwise combination of the accumulators
-#pragma unroll
-    for (int w = RU / 2; w > 0; w >>= 1)
-#pragma unroll
-        for (int u = 0; u < w; ++u) acc[u] += acc[u + w];
-    L s = hsum<L>(acc[0]);
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < head) s = s + x[threadIdx.x];
-        if ((int64_t)threadIdx.x < n - tail0) s = s + x[tail0 + threadIdx.x];
-    }
-    return block_sum(s, lds4);
-}
-
 // The partials and their sum in one launch.
 template <typename L>
 __global__ __launch_bounds__(RT) void reduce_fast_one(const L *__restrict__ x, int64_t n, uint32_t *partials,
@@ -131,59 +88,6 @@ __global__ __launch_bounds__(RT) void reduce_fast_one(const L *__restrict__ x, i
         s = block_sum(s, lds4);
     }
     if (threadIdx.x == 0) result[0] = init + s;
-}
-
-// Hands a workgroup's partial of each variable, the steps of reduce_vars, to
-// put(v, operator, partial), which stores thread 0's.
-template <typename E, int NV, uint32_t SIG, typename Put>
-__device__ inline void vars_partials(const E *__restrict__ x, int64_t n, const RedVars &vars, E *lds4, Put put)
-{
-    using R = Red<E>;
-    using V = typename R::V;
-    constexpr int W = R::W;
-
-    int op[NV], sq[NV];
-    E acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        op[v] = SIG == SIG_RUNTIME ? vars.op[v] : (int)((SIG >> (4 * v)) & 3u);
-        sq[v] = SIG == SIG_RUNTIME ? vars.square[v] : (int)((SIG >> (4 * v + 2)) & 1u);
-        acc[v] = red_identity<E>(op[v]);
-    }
-    auto fold = [&](E t) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] = red_apply<E>(op[v], acc[v], sq[v] ? R::mul(t, t) : t);
-    };
-
-    // Aligned body of 16-byte vectors, up to W-1 leading and trailing scalars.
-    const uintptr_t addr = (uintptr_t)x;
-    int64_t head = (int64_t)(((16u - (unsigned)(addr & 15u)) & 15u) / sizeof(E));
-    if (head > n) head = n;
-    const int64_t nvec = (n - head) / W;
-    const int64_t tail0 = head + nvec * W;
-    const V *__restrict__ xv = reinterpret_cast<const V *>(x + head);
-    const int64_t stride = (int64_t)gridDim.x * RT;
-    int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x;
-    for (; i + (RU - 1) * stride < nvec; i += RU * stride) {
-        V t[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) t[u] = __builtin_nontemporal_load(xv + i + u * stride);
-#pragma unroll
-        for (int u = 0; u < RU; ++u)
-#pragma unroll
-            for (int e = 0; e < W; ++e) fold(t[u][e]);
-    }
-    for (; i < nvec; i += stride) {
-        const V t = __builtin_nontemporal_load(xv + i);
-#pragma unroll
-        for (int e = 0; e < W; ++e) fold(t[e]);
-    }
-    if (blockIdx.x == 0) {
-        if ((int64_t)threadIdx.x < head) fold(x[threadIdx.x]);
-        if ((int64_t)threadIdx.x < n - tail0) fold(x[tail0 + threadIdx.x]);
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) put(v, op[v], block_apply<E>(op[v], acc[v], lds4));
 }
 
 // The partials, folded and combined with the initial values in one launch.
@@ -224,34 +128,6 @@ __global__ __launch_bounds__(RT) void reduce_vars_one(const E *__restrict__ x, i
 #pragma unroll
         for (int v = 0; v < NV; ++v) result[v] = red_apply<E>(op[v], bits_as<E>(vars.init[v]), acc[v]);
     }
-}
-
-// Operator sets that are compiled: one variable (+, max, min; x or x*x), and
-// the pairs the paper's reduction loops use (SRAD's sum and sum of squares)
-// or that come as one (max and min); anything else decodes at run time.
-// Calls launch with the set as an integral constant.
-template <int NV, typename Launch> void with_operators(const RedVars &vars, Launch launch)
-{
-    uint32_t sig = 0;
-    for (int v = 0; v < NV; ++v) sig |= (uint32_t)(vars.op[v] | (vars.square[v] ? 4 : 0)) << (4 * v);
-    if constexpr (NV == 1) {
-        switch (sig) {
-        case 0x0: return launch(std::integral_constant<uint32_t, 0x0>{});
-        case 0x1: return launch(std::integral_constant<uint32_t, 0x1>{});
-        case 0x2: return launch(std::integral_constant<uint32_t, 0x2>{});
-        case 0x4: return launch(std::integral_constant<uint32_t, 0x4>{});
-        case 0x5: return launch(std::integral_constant<uint32_t, 0x5>{});
-        case 0x6: return launch(std::integral_constant<uint32_t, 0x6>{});
-        }
-    } else if constexpr (NV == 2) {
-        switch (sig) {
-        case 0x40: return launch(std::integral_constant<uint32_t, 0x40>{});  // sum, sum of squares
-        case 0x04: return launch(std::integral_constant<uint32_t, 0x04>{});  // sum of squares, sum
-        case 0x21: return launch(std::integral_constant<uint32_t, 0x21>{});  // max, min
-        case 0x12: return launch(std::integral_constant<uint32_t, 0x12>{});  // min, max
-        }
-    }
-    launch(std::integral_constant<uint32_t, SIG_RUNTIME>{});
 }
 
 // A number of one call's own, ARRIVALS and below zero, never 0: a counter,
