@@ -154,8 +154,9 @@ typedef struct acc_region_s *acc_region; /* opaque */
 
 /* ---- flags for acc_reduce_sum / accx_reduce_sum_dev --------------------- */
 #define ACC_REDUCE_FAST 0x0u  /* streaming pass (grid-stride 16-byte loads, one partial
-                                 per workgroup), then a one-workgroup launch that
-                                 adds the partials in index order */
+                                 per workgroup); the partials are added in index order
+                                 by the workgroup that arrives last, or (large sums,
+                                 calls under capture) by a second, one-workgroup launch */
 #define ACC_REDUCE_PLAIN 0x1u /* one element per thread + block tree, then a
                                  second one-block launch over the partials */
 
@@ -415,8 +416,9 @@ ACCX_API acc_status accx_reduce_dev_noalloc(acc_dtype t, const void *dX, int64_t
  * output tiles and reduction chunks from them.  Every matmul reads its
  * operands as they are when the batch is launched, also where an item of the
  * batch overwrites them (the prologue copies those).  A matmul runs 64 x 64
- * tiles when its LEN is below a threshold, else 128 x 128 (with
- * ACC_BATCH_PREC_AUTO also 256 x 128) tiles, or the tile its flags force;
+ * tiles when its LEN is below a threshold, else 128 x 128 tiles (with
+ * ACC_BATCH_PREC_AUTO also 256 x 128, in batches with enough of them to keep
+ * the persistent workgroups busy), or the tile its flags force;
  * ACC_BATCH_AUTOTUNE picks the threshold by timing the batch itself,
  * otherwise it is 512.  Matmuls in a batch use the six-product bf16x3 split
  * (or ACC_PREC_AUTO's steps, ACC_BATCH_PREC_AUTO);

@@ -15,18 +15,18 @@
 //     so that HBM-bound and matrix-core-bound work share the CUs.
 //
 // What bounds it: 512 matmuls (LEN uniform over 64, 128, ..., 1024) and 256
-// sums (2^16 to 2^24 elements) take 1.60 ms, 1.33 ms with the matmuls alone
-// and 0.50 ms with the sums alone (6.3 TB/s).  They took 2.54 ms while a
+// sums (2^16 to 2^24 elements) take 1.49 ms, 1.28 ms with the matmuls alone
+// and 0.49 ms with the sums alone (6.4 TB/s).  They took 2.54 ms while a
 // prepass packed every operand (0.71 ms) for tiles fed by direct-to-LDS
 // loads (1.83 ms); queues per XCD instead of one: 1.85 -> 1.80 ms; 256 x 128
 // tiles beside 128 x 128: 1.80 -> 1.65 ms; a second set of loads in flight in
-// the sums: 1.65 -> 1.60 ms.  In the tile loop (128 x 128, LEN = 4096) the
-// matrix cores are busy 44 % of the cycles, the vector units 34 % (the split
-// is two thirds of that) and the LDS 38 %: with two wavefronts per SIMD their
-// times add up more than they overlap.  Without the split the tile would run
-// 13 % faster, without its loads 30 %, without the probe 12 %; three
-// workgroups per CU of 16-element stages gained 5 % on 128 x 128, less than
-// the larger tile, which they leave no registers for.
+// the sums: 1.65 -> 1.60 ms; the probe on the float64 matrix cores: 1.60 ->
+// 1.51 ms.  In the tile loop (128 x 128, LEN = 4096) the matrix cores are busy
+// 44 % of the cycles, the vector units 34 % (the split is two thirds of that)
+// and the LDS 38 %: with two wavefronts per SIMD their times add up more than
+// they overlap.  Without the split the tile would run 13 % faster, without its
+// loads 30 %; three workgroups per CU of 16-element stages gained 5 % on 128 x
+// 128, less than the larger tile, which they leave no registers for.
 //
 // A reduction's chunk partials are combined by the workgroup that finishes
 // its last chunk (atomic ticket), in chunk order, so results do not depend
@@ -50,7 +50,11 @@ namespace {
 using namespace dev;
 
 constexpr int BT = 256;              // threads per workgroup (both kernels)
-constexpr int WG_PER_CU = 2;         // persistent workgroups per CU (LDS: 2 x 72 KB; 256 registers each)
+// Persistent workgroups per CU (LDS: 2 x 72 KB).  They leave a lane 256
+// registers; the AUTO kernel's 256 x 128 branch needs 28 more, which it keeps
+// in 116 bytes of scratch (3 and 16 bytes without that branch, none with six
+// products).
+constexpr int WG_PER_CU = 2;
 constexpr uint32_t UNIT_RED = 0x80000000u;
 
 // K elements per LDS stage: a stage holds 24 matrix instructions per

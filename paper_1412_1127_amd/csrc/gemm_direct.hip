@@ -1,7 +1,8 @@
 // The float32 nest on the bf16 matrix cores in one launch, straight from the
 // float32 operands (direct_tile.h): no prepass, no packed operands, and with
 // ACC_PREC_AUTO the float64 probe and the correction of a tile in the
-// workgroup that computed it.
+// workgroup that computed it (in several rounds of tiles with long loops, the
+// corrections in a second launch that shares them among all CUs).
 //
 // A workgroup is G groups of four wavefronts on one output tile; each group
 // runs its own share of the K loop with its own LDS stages, and the groups'
@@ -13,14 +14,14 @@
 // (partial sums in a workspace, added in part order by the last part).
 //
 // Measured (us per call, calls back to back; before: the packed path's two to
-// four launches): AUTO LEN = 256 17.8 -> 9.2, 1000 34.8 -> 18.5, 2048 98 ->
-// 68, 512 x 4096 x 4096 143 -> 71 (241 TFLOP/s float32, 723 of bf16
-// products); six products LEN = 2048 105 -> 93 (1105 TFLOP/s of bf16
-// products).  What bounds them: up to LEN = 512 the launch and a handful of
-// memory round trips (64 x 64 x 64 takes 6.8 us, of which the probe 1.9); at
-// 1000, one 64 x 64 tile per CU, the loads (32 KB per 64 k and CU, 12.7 ns
-// per k) and 3.5 us of probe; at 2048 the tile loop itself, where the matrix
-// cores wait for the split and the loads as in the batch kernel.
+// four launches): AUTO LEN = 256 17.8 -> 9.1, 1000 39 -> 17, 2048 96 -> 62,
+// 512 x 4096 x 4096 127 -> 70 (245 TFLOP/s float32, 730 of bf16 products); six
+// products LEN = 2048 104 -> 88 (1170 TFLOP/s of bf16 products).  What bounds
+// them: up to LEN = 512 the launch and a handful of memory round trips (64 x
+// 64 x 64 takes 6.6 us, of which the probe 1.9); at 1000, one 64 x 64 tile per
+// CU, the loads (32 KB per 64 k and CU, 12.7 ns per k) and 3.5 us of probe; at
+// 2048 the tile loop itself, where the matrix cores wait for the split and the
+// loads as in the batch kernel.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -157,9 +158,9 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
 // round of units leaves the least of the grid idle (LEN = 4096, row-scaled, 92
 // sub-tiles: five parts in one round 467 us a call, eight in two 37 more, packed
 // 64 x 64 correction 492; 20 % of LEN = 6144 marked, 468 sub-tiles, one part
-// 1.57 ms, five 1.78), none shorter than 64.  Parts leave their sums in `partials`, the last one (the record's
-// ticket) adds them in part order to C; the result does not depend on the
-// list's order.  Before, every 64 x 64 sub-tile of C had a workgroup that read
+// 1.57 ms, five 1.78), none shorter than 64.  Parts leave their sums in
+// `partials`, the last one (the record's ticket) adds them in part order to C;
+// the result does not depend on the list's order.  Before, every 64 x 64 sub-tile of C had a workgroup that read
 // its record and, if marked, ran the packed three-plane tile over all of K:
 // 1104 of them on the 768 slots of the chip in two unequal rounds, 0.74 ms on
 // the row-scaled LEN = 8192 inputs (69 of 1024 tiles marked, 222 GFLOP); now

@@ -15,8 +15,8 @@
 // bytes instead of one.
 //
 // Measured, us per call, before and after (values in [-16, 16] / full range):
-// LEN = 64 14.9 -> 5.6 / 18.3 -> 5.4; 256 16.7 -> 7.5 / 23.7 -> 8.3; 1000 18.7 ->
-// 17.1 / 61 -> 21.7; 128 x 128 x 4096 20.9 -> 15.4 / 132 -> 17.4.  Up to 512 the
+// LEN = 64 10.5 -> 4.7 / 16.7 -> 5.1; 256 12.2 -> 7.2 / 23.2 -> 8.1; 1000 17.0 ->
+// 16.1 / 58 -> 21; 128 x 128 x 4096 18.8 -> 15.1 / 131 -> 16.9.  Up to 512 the
 // launch and the memory round trips bound it; at 1000 (one 64 x 64 tile per CU)
 // the conversion and the 32 KB a stage loads.  Before the two wavefronts of a
 // SIMD took the halves of a step in opposite order, ten products on 128 x 128

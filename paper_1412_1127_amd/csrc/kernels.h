@@ -191,9 +191,9 @@ hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t s);
 // tiles (tile); products as above (6, 5 or 3).  rec non-null: the AUTO steps
 // (three products, float64 probe of each tile with threshold tau into rec,
 // and, if corrects, correction of the marked ones; without it 128 x 128 tiles
-// only) in the same launch.  sk.parts > 1: the K
-// range in that many workgroups per tile, with split_k_bytes(tile, ...) of
-// workspace.  lda and ldb at most DIRECT_MAX_LD (32-bit offsets in a tile).
+// only) in the same launch.  sk.parts > 1: the K range in that many workgroups
+// per tile, with split_k_bytes(tile, ...) of workspace.  lda and ldb at most
+// DIRECT_MAX_LD (32-bit offsets in a tile).
 constexpr int64_t DIRECT_MAX_LD = (int64_t)1 << 19;
 hipError_t launch_gemm_direct(const float *a, const float *b, float *c, const GemmShape &sh, int products, int tile,
                               double tau, ProbeRecord *rec, bool corrects, hipStream_t s, const SplitK &sk = SplitK());
@@ -204,8 +204,8 @@ hipError_t launch_gemm_i8_direct(const int32_t *a, const int32_t *b, int32_t *c,
                                  hipStream_t s, const SplitK &sk = SplitK());
 // The correction after a three-product pass and its probe: C += the three
 // missing products on the marked tiles, those in the records' list if listed,
-// else (at most CORR_SCAN records) those whose record says so (rec: one record per
-// tile of `tile`, 128 x 128 or larger), straight from the float32 operands
+// else (at most CORR_SCAN records) those whose record says so (rec: one record
+// per tile of `tile`, 128 x 128 or larger), straight from the float32 operands
 // (lda, ldb <= DIRECT_MAX_LD).  work: work_bytes for partial sums (256-byte
 // aligned) of at most max_parts K parts per sub-tile.
 constexpr int CORR_SCAN = 1024;
@@ -264,7 +264,7 @@ struct BatchQueue {
 };
 int batch_tile_supported(int tile);
 int batch_workgroups();
-// Zero the queue's counter and the reductions' tickets and make the operand
+// Zero the queues' counters and the reductions' tickets and make the operand
 // copies; must precede every persistent launch on its stream.
 hipError_t launch_batch_prologue(const BatchQueue &q, hipStream_t s);
 hipError_t launch_batch_persistent(const BatchQueue &q, hipStream_t s);

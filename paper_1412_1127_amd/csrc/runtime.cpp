@@ -541,16 +541,16 @@ int resolve_tile(int t, const GemmShape &sh, uint32_t flags, int limbs)
 // 0: the packed path.  The direct tile splits and loads its operands itself,
 // so it pays while its tiles come in one round of workgroups (one per CU), or
 // little more: measured, us per call, packed against direct, AUTO: LEN = 256
-// 17.8 / 9.1, 1000 39 / 18, 1531 71 / 42, 2048 96 / 64, 3072 (2.3 rounds of
-// 128 x 128) 280 / 239, 3500 (3.1 rounds) 358 / 357; six products: 256 10.8 /
-// 7.5, 1000 29 / 19, 2048 105 / 89, 2200 (1.3 rounds) 165 / 165.  Beyond one
+// 17.8 / 9.1, 1000 39 / 17, 1531 71 / 42, 2048 96 / 62, 3072 (2.3 rounds of
+// 128 x 128) 282 / 244, 3500 (3.1 rounds) 358 / 357; six products: 256 10.6 /
+// 7.3, 1000 29 / 19, 2048 104 / 88, 2200 (1.3 rounds) 165 / 165.  Beyond one
 // round the packed path's larger tiles win: 4096 x 4096 x 512 75 / 87.
 // Between one and 1.4 rounds the last round is nearly empty, which on long
 // loops costs more than the prepass (2169 x 2169 x 1800 102 / 108, 2269 x 2269
 // x 4756 230 / 255, but 2100 x 2100 x 1040 73 / 68 and 2400 x 2400 x 1344 87 /
 // 80).  Without the probe (CHEAP3) the packed path is two launches, and wins
 // up to two rounds (2060 93 / 98, 2100 x 2100 x 1040 53 / 55) and on short
-// loops (3000 x 3000 x 16 20.0 / 22.1), but not beyond (3072 241 / 219).
+// loops (3000 x 3000 x 16 20.0 / 22.1), but not beyond (3072 241 / 213).
 // Among 64 x 64 tiles, 128 x 128 tiles and K parts the estimate below picks:
 // a base (launch, first loads, probe, stores), the same again, but for the
 // launch, for each further round, and a time per k and round, all fitted to
@@ -2508,9 +2508,9 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
     if (e == hipSuccess) e = hipDeviceSynchronize();
     int64_t threshold = kBatchDefaultThreshold;
     if (e == hipSuccess && (flags & ACC_BATCH_AUTOTUNE) && !mats.empty()) {
-        // Autotune the tile policy on this batch itself: pack once, then time
-        // the persistent kernel under each LEN threshold between the 64 x 64
-        // and 128 x 128 tiles (best of two runs after a warm-up run each).
+        // Autotune the tile policy on this batch itself: time the persistent
+        // kernel under each LEN threshold between the 64 x 64 and the larger
+        // tiles (best of two runs after a warm-up run each).
         e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (e == hipSuccess) e = hipEventCreate(&e0);
@@ -2554,8 +2554,8 @@ acc_status accx_batch_create(const accx_batch_item *items, int nitems, uint32_t 
         }
     }
     for (const accx::BatchMat &m : mats) info.tiles += (int64_t)m.tiles_m * m.tiles_n;
-    // Capture the two kernels into one graph (no memset node: the kernels
-    // leave every counter at zero).
+    // Capture the two kernels into one graph (no memset node: the prologue
+    // zeroes every counter).
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
