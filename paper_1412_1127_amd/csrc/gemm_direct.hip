@@ -160,12 +160,14 @@ __global__ __launch_bounds__(256 * G) void gemm_direct(DirectArgs g, DirectPlan 
 // 64 x 64 correction 492; 20 % of LEN = 6144 marked, 468 sub-tiles, one part
 // 1.57 ms, five 1.78), none shorter than 64.  Parts leave their sums in
 // `partials`, the last one (the record's ticket) adds them in part order to C;
-// the result does not depend on the list's order.  Before, every 64 x 64 sub-tile of C had a workgroup that read
-// its record and, if marked, ran the packed three-plane tile over all of K:
-// 1104 of them on the 768 slots of the chip in two unequal rounds, 0.74 ms on
-// the row-scaled LEN = 8192 inputs (69 of 1024 tiles marked, 222 GFLOP); now
-// 0.46 ms.  The split into three planes bounds it (88 vector instructions for
-// 12 matrix instructions of a wavefront and 16 k).
+// the result does not depend on the list's order.  Before, every 64 x 64
+// sub-tile of C had a workgroup that read its record and, if marked, ran the
+// packed three-plane tile over all of K: 1104 of them on the 768 slots of the
+// chip in two unequal rounds, 0.71 ms on the row-scaled LEN = 8192 inputs (69
+// of 1024 tiles marked, 222 GFLOP); now 0.49 ms, beside 0.55 with C and the
+// parts' sums loaded one element after the other.  The split into three planes
+// bounds it (88 vector instructions for 12 matrix instructions of a wavefront
+// and 16 k).
 // After the direct kernel in more than one round of tiles there is no list:
 // every workgroup makes it from the records, in the order of the tiles.
 struct CorrPlan {
